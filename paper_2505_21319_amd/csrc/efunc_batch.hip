@@ -33,7 +33,7 @@ struct efunc_batch {
     BatchShape* d_bs = nullptr;
     int* goff = nullptr;
     int2* gtiles = nullptr;
-    int* ngt = nullptr;
+    int* gcount = nullptr;  // tiles per cost bucket
     int* gqueue = nullptr;
     int64_t* step = nullptr;
     std::vector<void*> allocs;
@@ -139,10 +139,10 @@ hipError_t enqueue_iteration(efunc_batch* b, const AdamParams& ap, hipStream_t s
         if (e == hipSuccess) e = hipStreamWaitEvent(s, b->ev_join[k], 0);
     }
     if (e != hipSuccess) return e;
-    e = run_batch_order(b->d_bs, b->S, b->max_tiles_max, b->goff, b->gtiles, b->ngt, b->gqueue, s);
+    e = run_batch_order(b->d_bs, b->S, b->max_tiles_max, b->goff, b->gtiles, b->gcount, b->gqueue, s);
     if (e != hipSuccess) return e;
     if (t0) (void)hipEventRecord(t0, s);
-    e = run_batch_tiles(b->ctx[0]->layout.degree, b->d_tab, b->S, b->gtiles, b->ngt, b->gqueue,
+    e = run_batch_tiles(b->ctx[0]->layout.degree, b->d_tab, b->S, b->gtiles, b->gcount, b->gqueue,
                         b->num_cu * b->tune.blocks_per_cu, b->num_cu, t1, s);
     if (e != hipSuccess) return e;
     e = run_batch_finish(b->d_bs, b->S, b->nmax, b->step, ap, s);
@@ -203,7 +203,7 @@ int efunc_batch_create(const efunc_config* cfgs, const int64_t* max_points, int3
     if (e == hipSuccess) e = balloc(b, &b->d_bs, n_shapes);
     if (e == hipSuccess) e = balloc(b, &b->goff, (size_t)n_shapes * 128);
     if (e == hipSuccess) e = balloc(b, &b->gtiles, (size_t)b->tiles_total);
-    if (e == hipSuccess) e = balloc(b, &b->ngt, 1);
+    if (e == hipSuccess) e = balloc(b, &b->gcount, 128);
     if (e == hipSuccess) e = balloc(b, &b->gqueue, 1);
     if (e == hipSuccess) e = balloc(b, &b->step, 1);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);

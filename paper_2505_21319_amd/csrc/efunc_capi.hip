@@ -151,13 +151,21 @@ size_t carve_work(const efunc_config& cfg, const Layout& layout, int64_t max_poi
     k.take(w.tiles, w.max_tiles);
     k.take(w.tiles_tmp, w.max_tiles);
     k.take(w.tbucket, w.max_tiles);
-    k.take(w.chist, nkeys);
-    k.take(w.cstart, nkeys + 1);
+    // the loss sums of the tile kernel's items take the place of the tile
+    // sort's counts, which are no longer read when it runs; cutting heavy
+    // tiles adds at most 1 / PIECE_SHARE items per workgroup slot
+    {
+        const int64_t extra = (int64_t)(1.25 / PIECE_SHARE * (4.0 * w.num_cu)) + 1, cut = (MAX_PIECES - 1) * w.max_tiles;
+        const int64_t items = w.max_tiles + (extra < cut ? extra : cut);
+        const int64_t words = 2 * nkeys + 1 > 4 * items ? 2 * nkeys + 1 : 4 * items;
+        k.take(w.chist, words);
+        w.cstart = w.chist ? w.chist + nkeys : nullptr;
+        w.lpart = reinterpret_cast<double2*>(w.chist);
+    }
     k.take(w.ps, mp);
     k.take(w.pv, mp);
     k.take(w.pidx, mp);
     k.take(w.fb, mp);
-    k.take(w.lpart, w.max_tiles);
     k.take(w.scan_blk, nblk + 1);
     k.take(w.grad, (int64_t)layout.nch * I);
     k.take(w.gslot, layout.moved ? (int64_t)flush_slots(layout.degree) * I : 1);

@@ -11,7 +11,7 @@ constexpr int BLOCK = 256;      // threads per workgroup (4 wave64)
 constexpr int PMAX = 512;       // queries per tile (two per thread at most)
 constexpr int PMIN_CAP = 128;   // smallest tile query cap the workspace is sized for
 constexpr int KC = 256;         // keys per LDS chunk
-constexpr int MAXSEG = 1024;    // moved-key row segments per group (a window has (2W+2)^2 rows)
+constexpr int MAXSEG = 512;     // moved-key row segments per group (a window has (2W+2)^2 rows)
 constexpr int WMAX = 40;        // largest window half-width
 constexpr int SCAN_TILE = 1024; // elements per block in the prefix scans
 constexpr int PSPLIT = 8;       // sub-counters per cell in the query histogram
@@ -19,6 +19,13 @@ constexpr int LBIN_MAX = 32768; // query sort keys one workgroup bins in LDS (12
 constexpr int LBIN_BLOCK = 1024;  // threads per LDS-binning workgroup
 constexpr int LBIN_NW = 64;     // most LDS-binning workgroups (rows of the key histogram)
 constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
+// Heavy tiles are cut so that no item of the tile kernel's queue is estimated
+// (window keys x queries) above PIECE_SHARE of a workgroup slot's fair share of
+// the work, nor cut below PIECE_LEAST (about 20 us of one workgroup; smaller
+// items pay more for gathering their keys again than the balance gives).
+constexpr int MAX_PIECES = 8;
+constexpr float PIECE_SHARE = 0.75f;
+constexpr float PIECE_LEAST = 1e5f;
 constexpr int SLICE_KEYS = 8;   // slice-index sort keys per cost bucket in the tile order
 constexpr int RS_TILE = 4 * BLOCK;  // elements per workgroup of the deterministic radix sort
 constexpr float LOG2E = 1.4426950408889634f;
@@ -34,7 +41,8 @@ struct DevStats {
     unsigned int bgmax_bits;  // max beta over grid keys
     int W;                    // window half-width of this call
     int nonfinite;            // non-finite parameters seen by the key preparation
-    int pad0[28];
+    int nitems;               // work items of the tile kernel
+    int pad0[27];
     int queue;                // tile work-queue head
     int pad1[31];
     int nfb;                  // queries appended to the fallback list
@@ -137,7 +145,7 @@ struct Work {
     float4* pv;           // [max_points] {O, lse, 0, 0} (backward inputs)
     int* pidx;            // [max_points] original query index
     int* fb;              // [max_points] fallback list (sorted query positions)
-    double2* lpart;       // [max_tiles]  per-tile loss sums
+    double2* lpart;       // [max_tiles + extra_items]  per-item loss sums (overlies chist and cstart)
     int* scan_blk;        // [ceil(max(8 NB3 PSPLIT, 128 SLICE_KEYS nch) / SCAN_TILE) + 1] scan block sums
     float* grad;          // [nch I] internal gradient of efunc_fit_step (kept zero)
     float* gslot;         // [nfl I] moved keys' gradient by binned record, flush-slot order (kept zero)
@@ -202,7 +210,7 @@ struct TileArgs {
     const float4* pv;
     const int* pidx;
     const int4* tiles;
-    const int* ntiles;  // &tstart[NB3]
+    int slots;          // workgroups that run at a time
     int* fb;
     double2* lpart;
     DevStats* st;
@@ -223,7 +231,7 @@ struct BatchShape {
     const int2* tbucket;   // cost bucket and rank of each tile (block order)
     const int* ntiles;
     const DevStats* st;
-    const double2* lpart;
+    double2* lpart;
     double invJ;
     double* loss_out;      // [2] MSE, L1 (may be null)
     float* theta;
@@ -253,8 +261,8 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered);
 // tiles, one persistent tile kernel and one fallback kernel over all of them,
 // per-shape loss reduction, AdamW with the step read from device memory.
 hipError_t run_batch_order(const BatchShape* bs, int S, int64_t max_tiles, int* goff, int2* gtiles,
-                           int* ngt, int* gqueue, hipStream_t s);
-hipError_t run_batch_tiles(int degree, const TileArgs* tab, int S, const int2* gtiles, const int* ngt,
+                           int* gcount, int* gqueue, hipStream_t s);
+hipError_t run_batch_tiles(int degree, const TileArgs* tab, int S, const int2* gtiles, const int* gcount,
                            int* gqueue, int grid, int fgrid, hipEvent_t ev_stop, hipStream_t s);
 hipError_t run_batch_finish(const BatchShape* bs, int S, int64_t nmax, const int64_t* step,
                             const AdamParams& ap, hipStream_t s);

@@ -1274,7 +1274,9 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 
 // One tile: window, forward (Alg. 1), loss, backward (Alg. 2) and flush.
 // td is the tile descriptor, tile its index in a.tiles (loss partial slot);
-// W and bmin2 (smallest beta in log2 units) come from the shape's DevStats.
+// W and bmin2 (smallest beta in log2 units) come from the shape's DevStats;
+// whole is the range of queries of the tile that td is (a piece of), lanes the
+// forward's lanes per query of a piece (0: by the number of queries).
 //
 // Keys reach the pair loops in two steps.  The window's candidates are
 // visited in chunks of KC (grid vertices first, then the moved keys row
@@ -1285,8 +1287,9 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 // the pair loops run over that batch, so every batch but the last holds KC
 // kept keys whatever fraction of the window survives the cull.
 template <int MODE, bool QGRAD, int DEG>
-__device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, const int4 td, const int tile,
-                                         const int W, const float bmin2, PairCount& pc, const bool half_batches)
+__device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, const int4 td, const int2 whole,
+                                         const int lanes, const int tile, const int W, const float bmin2, PairCount& pc,
+                                         const bool half_batches, const bool add_loss)
 {
     static_assert(KC == BLOCK, "one staged key per thread");
     constexpr int GW = gk_width(DEG), MW = mk_width(DEG);
@@ -1523,9 +1526,16 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         // ---- reference exponent: largest corner logit of the home cell
         int need_exact = 0;
         float bl[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, INFINITY};
-        for (int p = tid; p < P; p += BLOCK) {
-            const float4 pq = S.pq[p];
-            const float4 qa = a.ps[p0 + p];  // absolute position: the binning's home cell
+        // over the whole tile: whether the exact maximum is needed is decided
+        // for all its pieces together, and the box of a piece whose queries
+        // have several lanes each is the tile's (a lane takes every Sf-th key
+        // that the box keeps)
+        for (int w = tid; w < whole.y; w += BLOCK) {
+            const float4 qa = a.ps[whole.x + w];
+            const int p = whole.x + w - p0;
+            const bool own = p >= 0 && p < P;
+            const float x = qa.x - oxf, y = qa.y - oyf, z = qa.z - ozf;
+            // absolute position: the binning's home cell
             const int hx = cell_of(qa.x, g), hy = cell_of(qa.y, g), hz = cell_of(qa.z, g);
             float M0 = -INFINITY;  // without grid keys: the exact pass below
 #pragma unroll
@@ -1534,16 +1544,17 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 const int ix = hx + (c8 >> 2), iy = hy + ((c8 >> 1) & 1), iz = hz + (c8 & 1);
                 const int vid = (ix * R + iy) * R + iz;
                 const float nb = a.gk[GW * (int64_t)vid].x;
-                const float dx = pq.x - (g.tlat[ix] - oxf);
-                const float dy = pq.y - (g.tlat[iy] - oyf);
-                const float dz = pq.z - (g.tlat[iz] - ozf);
+                const float dx = x - (g.tlat[ix] - oxf);
+                const float dy = y - (g.tlat[iy] - oyf);
+                const float dz = z - (g.tlat[iz] - ozf);
                 M0 = fmaxf(M0, nb * fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
             }
-            S.pv[p] = make_float4(0.0f, 0.0f, 0.0f, M0);
             // exp2(s - M0) <= 2^-M0 per key; keep the sum of K such terms finite
             if (!(-M0 + log2f((float)Kg + (float)Kmt + 1.0f) < 120.0f)) need_exact = 1;
-            bl[0] = fminf(bl[0], pq.x); bl[1] = fminf(bl[1], pq.y); bl[2] = fminf(bl[2], pq.z);
-            bl[3] = fmaxf(bl[3], pq.x); bl[4] = fmaxf(bl[4], pq.y); bl[5] = fmaxf(bl[5], pq.z);
+            if (own) S.pv[p] = make_float4(0.0f, 0.0f, 0.0f, M0);
+            if (!own && lanes) continue;
+            bl[0] = fminf(bl[0], x); bl[1] = fminf(bl[1], y); bl[2] = fminf(bl[2], z);
+            bl[3] = fmaxf(bl[3], x); bl[4] = fmaxf(bl[4], y); bl[5] = fmaxf(bl[5], z);
             bl[6] = fminf(bl[6], M0);
         }
         const int exact = __syncthreads_or(need_exact);
@@ -1555,7 +1566,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         // and queries [BLOCK, P) (at most BLOCK - 1 of them) with Sf2 lanes
         // each; the partial sums of query p live in slots slot(p, 0..n-1).
         const int P1 = min(P, BLOCK), P2 = P - P1;
-        const int Sf = max(1, BLOCK / P1);
+        const int Sf = lanes ? lanes : max(1, BLOCK / P1);
         const int Sf2 = P2 > 0 ? max(1, BLOCK / P2) : 1;
         const int pme = tid / Sf, ph = tid - pme * Sf;
         const int pme2 = tid / Sf2, ph2 = tid - pme2 * Sf2;
@@ -1670,7 +1681,14 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         if (MODE == MODE_FIT) {
             lsq = block_sum(lsq, S.dsc);
             lab = block_sum(lab, S.dsc);
-            if (tid == 0) a.lpart[tile] = make_double2(lsq, lab);
+            if (tid == 0) {
+                if (add_loss) {  // the pieces of a batched tile share its slot
+                    unsafeAtomicAdd(&a.lpart[tile].x, lsq);
+                    unsafeAtomicAdd(&a.lpart[tile].y, lab);
+                } else {
+                    a.lpart[tile] = make_double2(lsq, lab);
+                }
+            }
         }
         __syncthreads();
 
@@ -1884,26 +1902,154 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     pc.bwd_moved += bwd_moved;
 }
 
-// Persistent tile kernel of one shape: workgroups pull tiles (heaviest
+// Work items of the queue.  The tiles are sorted heaviest first by cost bucket
+// (128 log-spaced buckets); a tile much heavier than a workgroup slot's fair
+// share of the work would still run when the others have finished, so the
+// tiles of the heavy buckets are cut into pieces, each an item of its own that
+// takes a range of the tile's queries.  Items are numbered by descending
+// bucket, inside a bucket piece by piece (the pieces of a tile share its keys:
+// apart, they don't add to the same gradient records at once).
+// Where moved keys crowd a surface a few tiles keep thousands of keys: with
+// whole tiles the heaviest one set the kernel's time in every call of up to
+// a few million queries.  Tile kernel at 32^3, whole tiles and cut: fit of 2^21
+// points 1664 and 1056 us, normals at 300,007 points 825 and 370 us, eval of
+// 128^3 lattice points 727 and 436 us; 32,768 points forward and backward 194
+// and 138 us each; shares of 0.25 to 1.0 of a slot's measured within 6 %, 0.12
+// 30 % slower.
+struct Items {
+    int first[129];   // by descending bucket: first item; [128] their number
+    int tfirst[128];  // first tile
+    int pieces[128];  // pieces per tile
+};
+
+// From the tiles per bucket, for a launch whose workgroups fill slots slots.
+__device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bcount, int slots, float* fsh, int* ish)
+{
+    const int i = threadIdx.x;
+    const int cnt = i < 128 ? bcount[127 - i] : 0;
+    const float cost = exp2f(0.25f * ((float)(127 - i) + 0.5f));
+    const float total = block_sum(i < 128 ? (float)cnt * cost : 0.0f, fsh);
+    const float share = fmaxf(PIECE_SHARE * total / (float)slots, PIECE_LEAST);
+    const int k = cost > share ? (int)fminf(ceilf(cost / share), (float)MAX_PIECES) : 1;
+    int tot;
+    const int t0 = block_excl_scan(cnt, ish, &tot);
+    const int f0 = block_excl_scan(i < 128 ? cnt * k : 0, ish, &tot);
+    if (i < 128) {
+        I.first[i] = f0;
+        I.tfirst[i] = t0;
+        I.pieces[i] = k;
+    }
+    if (i == 0) I.first[128] = tot;
+    __syncthreads();
+}
+
+// Item q's tile, piece and pieces of the tile asked for.
+__device__ __forceinline__ int find_item(const Items& I, int q, int& piece, int& pieces)
+{
+    int lo = 0, hi = 127;  // the last bucket that starts at or before q
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (I.first[mid] <= q) lo = mid; else hi = mid - 1;
+    }
+    const int r = q - I.first[lo];
+    pieces = I.pieces[lo];
+    const int cnt = (I.first[lo + 1] - I.first[lo]) / pieces;
+    piece = r / cnt;
+    return I.tfirst[lo] + r - piece * cnt;
+}
+
+// Piece j of at most k of tile td: its queries in td.y, td.z (none: false).
+// A fit keeps each query's lanes in the forward (lanes; 0: by the number of
+// queries) as in the whole tile, so that cutting a tile does not change the
+// order in which a query's terms are added: the tile's first 256 queries and
+// the rest are cut apart, and each only if its queries have one lane.
+template <int MODE>
+__device__ __forceinline__ bool take_piece(int4& td, int j, int k, int& lanes)
+{
+    lanes = 0;
+    const int P = td.z;
+    constexpr int LEAST = MODE == MODE_FIT ? 64 : 32;  // queries per piece
+    if (MODE != MODE_FIT) {
+        k = max(1, min(k, (P + LEAST - 1) / LEAST));
+        if (j >= k) return false;
+        const int lo = j * P / k, hi = (j + 1) * P / k;
+        td.y += lo;
+        td.z = hi - lo;
+        return true;
+    }
+    if (k == 1 || P <= BLOCK / 2) return j == 0;
+    const int m1 = min(P, BLOCK), m2 = P - m1;
+    const int k2 = m2 > BLOCK / 2 ? max(1, min(k * m2 / P, (m2 + LEAST - 1) / LEAST)) : (m2 > 0 ? 1 : 0);
+    const int k1 = max(1, min(k - k2, (m1 + LEAST - 1) / LEAST));
+    if (j >= k1 + k2) return false;
+    if (j < k1) {
+        const int lo = j * m1 / k1, hi = (j + 1) * m1 / k1;
+        td.y += lo;
+        td.z = hi - lo;
+        lanes = 1;
+    } else {
+        const int i = j - k1, lo = i * m2 / k2, hi = (i + 1) * m2 / k2;
+        td.y += m1 + lo;
+        td.z = hi - lo;
+        lanes = m2 > BLOCK / 2 ? 1 : 0;
+    }
+    return true;
+}
+
+__device__ __forceinline__ int4 uniform(const int4 v)
+{
+    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+}
+
+// Persistent tile kernel of one shape: workgroups pull items (heaviest
 // first) from an atomic queue until it is empty.
 // Degree 2 holds more live state per query and fits three waves per SIMD.
 template <int MODE, bool QGRAD, int DEG>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 ? 3 : 4, 8))) void k_tile(TileArgs a)
 {
     __shared__ TileSmem<DEG> S;
-    const int ntiles = *a.ntiles;
-    const int W = a.st->W;
+    __shared__ Items I;
+    const int W = __builtin_amdgcn_readfirstlane(a.st->W);
     const float bmin2 = __uint_as_float(a.st->bmin_bits) * LOG2E;
+    plan_items(I, a.st->bcount, a.slots, S.fsc, S.isc);
+    const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
     PairCount pc;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) S.tile = atomicAdd(&a.st->queue, 1);
         __syncthreads();
-        const int tile = S.tile;
-        if (tile >= ntiles) break;
-        tile_run<MODE, QGRAD, DEG>(a, S, a.tiles[tile], tile, W, bmin2, pc, true);
+        const int item = __builtin_amdgcn_readfirstlane(S.tile);
+        if (item >= nitems) break;
+        int j, k, lanes;
+        const int t = __builtin_amdgcn_readfirstlane(find_item(I, item, j, k));
+        j = __builtin_amdgcn_readfirstlane(j);
+        k = __builtin_amdgcn_readfirstlane(k);
+        int4 td = uniform(a.tiles[t]);
+        const int2 whole = make_int2(td.y, td.z);
+        if (take_piece<MODE>(td, j, k, lanes))
+            tile_run<MODE, QGRAD, DEG>(a, S, td, MODE == MODE_FIT ? whole : make_int2(td.y, td.z), lanes, item, W, bmin2,
+                                       pc, true, false);
+        else if (MODE == MODE_FIT && threadIdx.x == 0)
+            a.lpart[item] = make_double2(0.0, 0.0);
     }
     flush_pairs(a.st, pc);
+}
+
+// A copy of *p, p the same for the whole wave, by scalar loads.
+__device__ __forceinline__ TileArgs uniform_args(const TileArgs* p)
+{
+    typedef const uint32_t __attribute__((address_space(4))) * cptr;
+    static_assert(sizeof(TileArgs) % 4 == 0, "copied by words");
+    const cptr src = (cptr)(uintptr_t)p;
+    union {
+        TileArgs a;
+        uint32_t w[sizeof(TileArgs) / 4];
+    } u;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(TileArgs) / 4; ++i) u.w[i] = src[i];
+    return u.a;
 }
 
 // Persistent tile kernel over a batch of shapes: one queue of (shape, tile)
@@ -1911,20 +2057,23 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
 // arguments.
 template <int DEG>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 ? 2 : 4, 8))) void k_tile_batch(
-    const TileArgs* __restrict__ tab, const int2* __restrict__ gtiles, const int* __restrict__ ngt,
-    int* __restrict__ gqueue)
+    const TileArgs* __restrict__ tab, const int2* __restrict__ gtiles, const int* __restrict__ gcount,
+    int slots, int* __restrict__ gqueue)
 {
     __shared__ TileSmem<DEG> S;
-    const int n = *ngt;
+    __shared__ Items I;
+    plan_items(I, gcount, slots, S.fsc, S.isc);
+    const int n = __builtin_amdgcn_readfirstlane(I.first[128]);
     PairCount pc;
     int cur = -1;  // shape whose pair counts pc holds
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) S.tile = atomicAdd(gqueue, 1);
         __syncthreads();
-        const int t = S.tile;
+        const int t = __builtin_amdgcn_readfirstlane(S.tile);
         if (t >= n) break;
-        const int2 e = gtiles[t];
+        int j, k, lanes;
+        const int2 e = gtiles[find_item(I, t, j, k)];
         const int sh = __builtin_amdgcn_readfirstlane(e.x);
         const int lt = __builtin_amdgcn_readfirstlane(e.y);
         if (sh != cur) {
@@ -1932,9 +2081,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
             pc = PairCount();
             cur = sh;
         }
-        const TileArgs& a = tab[sh];
-        tile_run<MODE_FIT, false, DEG>(a, S, a.tiles[lt], lt, a.st->W,
-                                       __uint_as_float(a.st->bmin_bits) * LOG2E, pc, false);
+        const TileArgs a = uniform_args(tab + sh);
+        int4 td = uniform(a.tiles[lt]);
+        const int2 whole = make_int2(td.y, td.z);
+        if (!take_piece<MODE_FIT>(td, __builtin_amdgcn_readfirstlane(j), __builtin_amdgcn_readfirstlane(k), lanes))
+            continue;
+        tile_run<MODE_FIT, false, DEG>(a, S, td, whole, lanes, lt, __builtin_amdgcn_readfirstlane(a.st->W),
+                                       __uint_as_float(a.st->bmin_bits) * LOG2E, pc, false, true);
     }
     if (cur >= 0) flush_pairs(tab[cur].st, pc);
 }
@@ -2191,13 +2344,12 @@ __global__ void k_count_uncertified(const DevStats* st, int64_t* out)
 constexpr int LF_BLOCK = 1024;
 
 __global__ __launch_bounds__(LF_BLOCK) void k_loss_finalize(const double2* __restrict__ lpart,
-                                                            const int* __restrict__ ntiles,
                                                             const DevStats* __restrict__ st,
                                                             const DetStats* __restrict__ det,
                                                             double invJ, double* __restrict__ out)
 {
     __shared__ double sh[LF_BLOCK / 64];
-    const int n = *ntiles;
+    const int n = st->nitems;
     double s2 = 0.0, s1 = 0.0;
     for (int t0 = threadIdx.x; t0 < n; t0 += 4 * LF_BLOCK) {
         double2 v[4];
@@ -2273,9 +2425,10 @@ __global__ void k_adam_fit(float* __restrict__ theta, float* __restrict__ m, flo
 // ------------------------------------------------------------------ batch
 // Global heavy-first order over the tiles of all shapes: offset of each
 // (shape, cost bucket) run in descending bucket order, shapes in index order
-// inside a bucket.  Also resets the batch queue.
+// inside a bucket; the tiles per bucket go to gcount.  Also resets the batch
+// queue.
 __global__ __launch_bounds__(BLOCK) void k_batch_offsets(const BatchShape* __restrict__ bs, int S,
-                                                         int* __restrict__ goff, int* __restrict__ ngt,
+                                                         int* __restrict__ goff, int* __restrict__ gcount,
                                                          int* __restrict__ gqueue)
 {
     __shared__ int sh[BLOCK / 64];
@@ -2291,13 +2444,12 @@ __global__ __launch_bounds__(BLOCK) void k_batch_offsets(const BatchShape* __res
             goff[s * 128 + b] = run;
             run += bs[s].st->bcount[b];
         }
-    if (tid == 0) {
-        *ngt = tot;
-        *gqueue = 0;
-    }
+    if (tid < 128) gcount[b] = c;
+    if (tid == 0) *gqueue = 0;
 }
 
-// gtiles[position] = (shape, index in the shape's block-order tile list)
+// gtiles[position] = (shape, index in the shape's block-order tile list); the
+// tiles' loss sums start from zero
 __global__ __launch_bounds__(BLOCK) void k_batch_scatter(const BatchShape* __restrict__ bs,
                                                          const int* __restrict__ goff,
                                                          int2* __restrict__ gtiles)
@@ -2308,6 +2460,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_scatter(const BatchShape* __res
     for (int t = blockIdx.x * BLOCK + threadIdx.x; t < n; t += gridDim.x * BLOCK) {
         const int2 b = tb[t];
         gtiles[goff[s * 128 + b.x] + b.y] = make_int2(s, t);
+        bs[s].lpart[t] = make_double2(0.0, 0.0);
     }
 }
 
@@ -2623,7 +2776,7 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered)
     a.pv = w.pv;
     a.pidx = w.pidx;
     a.tiles = ordered ? w.tiles : w.tiles_tmp;
-    a.ntiles = w.tstart + w.NB3;
+    a.slots = 4 * w.num_cu;
     a.fb = w.fb;
     a.lpart = w.lpart;
     a.st = w.st;
@@ -2695,9 +2848,9 @@ hipError_t run_tiles(const Work& w, const Problem& p, Mode mode, hipStream_t s)
 }
 
 hipError_t run_batch_order(const BatchShape* bs, int S, int64_t max_tiles, int* goff, int2* gtiles,
-                           int* ngt, int* gqueue, hipStream_t s)
+                           int* gcount, int* gqueue, hipStream_t s)
 {
-    k_batch_offsets<<<1, BLOCK, 0, s>>>(bs, S, goff, ngt, gqueue);
+    k_batch_offsets<<<1, BLOCK, 0, s>>>(bs, S, goff, gcount, gqueue);
     int64_t gx = (max_tiles + BLOCK - 1) / BLOCK;
     if (gx > 64) gx = 64;
     if (gx < 1) gx = 1;
@@ -2706,21 +2859,21 @@ hipError_t run_batch_order(const BatchShape* bs, int S, int64_t max_tiles, int* 
 }
 
 template <int DEG>
-static void launch_batch(const TileArgs* tab, int S, const int2* gtiles, const int* ngt, int* gqueue,
+static void launch_batch(const TileArgs* tab, int S, const int2* gtiles, const int* gcount, int* gqueue,
                          int grid, int fgrid, hipEvent_t ev_stop, hipStream_t s)
 {
-    k_tile_batch<DEG><<<grid, BLOCK, 0, s>>>(tab, gtiles, ngt, gqueue);
+    k_tile_batch<DEG><<<grid, BLOCK, 0, s>>>(tab, gtiles, gcount, 4 * fgrid, gqueue);
     if (ev_stop) (void)hipEventRecord(ev_stop, s);
     k_fallback_batch<DEG><<<fgrid, FB_BLOCK, 0, s>>>(tab, S);
 }
 
-hipError_t run_batch_tiles(int degree, const TileArgs* tab, int S, const int2* gtiles, const int* ngt,
+hipError_t run_batch_tiles(int degree, const TileArgs* tab, int S, const int2* gtiles, const int* gcount,
                            int* gqueue, int grid, int fgrid, hipEvent_t ev_stop, hipStream_t s)
 {
     switch (degree) {
-    case 0: launch_batch<0>(tab, S, gtiles, ngt, gqueue, grid, fgrid, ev_stop, s); break;
-    case 2: launch_batch<2>(tab, S, gtiles, ngt, gqueue, grid, fgrid, ev_stop, s); break;
-    default: launch_batch<1>(tab, S, gtiles, ngt, gqueue, grid, fgrid, ev_stop, s);
+    case 0: launch_batch<0>(tab, S, gtiles, gcount, gqueue, grid, fgrid, ev_stop, s); break;
+    case 2: launch_batch<2>(tab, S, gtiles, gcount, gqueue, grid, fgrid, ev_stop, s); break;
+    default: launch_batch<1>(tab, S, gtiles, gcount, gqueue, grid, fgrid, ev_stop, s);
     }
     return hipGetLastError();
 }
@@ -2750,7 +2903,7 @@ hipError_t run_step_advance(int64_t* step, hipStream_t s)
 
 hipError_t run_loss_finalize(const Work& w, int64_t J, double* loss_out, hipStream_t s)
 {
-    k_loss_finalize<<<1, LF_BLOCK, 0, s>>>(w.lpart, w.tstart + w.NB3, w.st, w.det, 1.0 / (double)J, loss_out);
+    k_loss_finalize<<<1, LF_BLOCK, 0, s>>>(w.lpart, w.st, w.det, 1.0 / (double)J, loss_out);
     return hipGetLastError();
 }
 
