@@ -1048,28 +1048,31 @@ struct KeyQ<2> {
     __device__ KeyQ() {}
 };
 
+// Four workgroups share a CU's 160 KB (degrees 0 and 1): below 40 KB.
 template <int DEG>
 struct TileSmem {
     static constexpr int NF = flush_slots(DEG);  // flush slots per key
+    static constexpr int FS = KC + 8;            // stride of a slot: 8 slots of 8 keys fall in 64 banks
     static constexpr int NQ = DEG == 2 ? KC : 1;
+    float4 kc[KC];    // key centre relative to the tile origin, nb = -beta log2(e)
+    float4 kv[KC];    // o, d.xyz
+    float4 kqa[NQ];   // degree 2: S_xx/2, S_yy/2, S_zz/2, S_xy
+    float2 kqb[NQ];   // degree 2: S_xz, S_yz
     union {
-        struct {
-            float4 kc[KC];    // key centre relative to the tile origin, nb = -beta log2(e)
-            float4 kv[KC];    // o, d.xyz
-            float4 kqa[NQ];   // degree 2: S_xx/2, S_yy/2, S_zz/2, S_xy
-            float2 kqb[NQ];   // degree 2: S_xz, S_yz
+        float fv[(DEG == 2 ? 14 : 8) * FS];  // backward flush: channel values of the staged keys
+        struct {              // forward: partial sums of the queries' lanes
+            float2 red[PMAX];
+            float redz[PMAX];
         };
-        float fv[NF * KC];    // backward flush: NF channel values per kept key
     };
-    int kid[KC];          // vertex index; -(vid + 1) for moved keys
-    int cand[2 * KC];     // tags of culled-in window keys awaiting a batch
-    float4 pq[PMAX];      // query relative to the tile origin, aux (target or dL/dO)
-    float4 pv[PMAX];      // O, lse2 (log2 units), g = dL/dO, reference exponent
-    float2 red[PMAX];
+    int kid[KC];          // tags of the staged keys
+    int cand[LOGCAP];     // tags of the window keys that the cull kept, in order
+    float4 pq[PMAX];      // query relative to the tile origin; target, then g = dL/dO (eval: certified)
+    float2 pv[PMAX];      // O, lse2 (log2 units); before the forward: 0, reference exponent
     int seg_src[MAXSEG];
     int seg_off[MAXSEG + 1];
     float box[BLOCK / 64][8];  // per-wave bounds of the contributing queries
-    int isc[BLOCK / 64];
+    int isc[2 * (BLOCK / 64)];
     float fsc[BLOCK / 64];
     double dsc[BLOCK / 64];
     int tile;
@@ -1135,43 +1138,87 @@ struct NAcc {
     static constexpr int n = DEG == 2 ? 14 : 8;
 };
 
-// Backward accumulation over the tile's queries for one key held in
-// registers: key-parallel, as in Alg. 2.  MOVED adds the centre gradient sums.
+// One pair of the backward: adds query (pq, pv)'s terms to a key's sums.
 template <bool MOVED, int DEG>
-__device__ __forceinline__ void bwd_key(const TileSmem<DEG>& S, int P, int ph, int Sb, float4 kc,
-                                        float4 kv, const KeyQ<DEG>& kq, float (&acc)[NAcc<DEG>::n])
+__device__ __forceinline__ void bwd_pair(const float4 pq, const float2 pv, const float4 kc, const float4 kv,
+                                         const KeyQ<DEG>& kq, float (&acc)[NAcc<DEG>::n])
 {
-#pragma unroll 2
-    for (int p = ph; p < P; p += Sb) {
-        const float4 pq = S.pq[p];
-        const float4 pv = S.pv[p];
-        const float dx = pq.x - kc.x, dy = pq.y - kc.y, dz = pq.z - kc.z;
-        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        const float w = ex2(fmaf(kc.w, r2, -pv.y));
-        const float f = poly<DEG>(kv, kq, dx, dy, dz);
-        const float del = pv.z * w;
-        const float u = del * (f - pv.x);
-        acc[0] += del;
-        if (DEG >= 1) {
-            acc[1] = fmaf(del, dx, acc[1]);
-            acc[2] = fmaf(del, dy, acc[2]);
-            acc[3] = fmaf(del, dz, acc[3]);
-        }
-        acc[4] = fmaf(u, r2, acc[4]);
-        if (MOVED) {
-            acc[5] = fmaf(u, dx, acc[5]);
-            acc[6] = fmaf(u, dy, acc[6]);
-            acc[7] = fmaf(u, dz, acc[7]);
-        }
-        if constexpr (DEG == 2) {
-            const float hx = 0.5f * del * dx, hy = 0.5f * del * dy;
-            acc[8] = fmaf(hx, dx, acc[8]);
-            acc[9] = fmaf(hy, dy, acc[9]);
-            acc[10] = fmaf(0.5f * del * dz, dz, acc[10]);
-            acc[11] = fmaf(del * dx, dy, acc[11]);
-            acc[12] = fmaf(del * dx, dz, acc[12]);
-            acc[13] = fmaf(del * dy, dz, acc[13]);
-        }
+    const float dx = pq.x - kc.x, dy = pq.y - kc.y, dz = pq.z - kc.z;
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float w = ex2(fmaf(kc.w, r2, -pv.y));
+    const float f = poly<DEG>(kv, kq, dx, dy, dz);
+    const float del = pq.w * w;
+    const float u = del * (f - pv.x);
+    acc[0] += del;
+    if (DEG >= 1) {
+        acc[1] = fmaf(del, dx, acc[1]);
+        acc[2] = fmaf(del, dy, acc[2]);
+        acc[3] = fmaf(del, dz, acc[3]);
+    }
+    acc[4] = fmaf(u, r2, acc[4]);
+    if (MOVED) {
+        acc[5] = fmaf(u, dx, acc[5]);
+        acc[6] = fmaf(u, dy, acc[6]);
+        acc[7] = fmaf(u, dz, acc[7]);
+    }
+    if constexpr (DEG == 2) {
+        const float hx = 0.5f * del * dx, hy = 0.5f * del * dy;
+        acc[8] = fmaf(hx, dx, acc[8]);
+        acc[9] = fmaf(hy, dy, acc[9]);
+        acc[10] = fmaf(0.5f * del * dz, dz, acc[10]);
+        acc[11] = fmaf(del * dx, dy, acc[11]);
+        acc[12] = fmaf(del * dx, dz, acc[12]);
+        acc[13] = fmaf(del * dy, dz, acc[13]);
+    }
+}
+
+// Backward accumulation over queries ph, ph + st, ... of the tile's P for one
+// key held in registers: key-parallel, as in Alg. 2.  MOVED adds the centre
+// gradient sums.  ST: the step when known at compile time (else 0): the pair
+// loop is bound by VALU issue, and with a fixed step its LDS addresses are
+// one register and immediate offsets instead of two additions per pair.
+template <bool MOVED, int ST, int DEG>
+__device__ __forceinline__ void bwd_key(const TileSmem<DEG>& S, int P, int ph, int st, const float4 kc,
+                                        const float4 kv, const KeyQ<DEG>& kq, float (&acc)[NAcc<DEG>::n])
+{
+    const int step = ST ? ST : st;
+    const int full = P / step;  // the same for all lanes
+    const float4* q = S.pq + ph;
+    const float2* v = S.pv + ph;
+    int i = 0;
+    for (; i + 4 <= full; i += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bwd_pair<MOVED, DEG>(q[u * step], v[u * step], kc, kv, kq, acc);
+        q += 4 * step;
+        v += 4 * step;
+    }
+    for (; i < full; ++i) {
+        bwd_pair<MOVED, DEG>(*q, *v, kc, kv, kq, acc);
+        q += step;
+        v += step;
+    }
+    if (ph < P - full * step) bwd_pair<MOVED, DEG>(*q, *v, kc, kv, kq, acc);
+}
+
+// x plus the x of the lane that CTRL pairs this one with (a DPP control).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x)
+{
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+// Sums over groups of 2^ls adjacent lanes, in every lane of the group.
+template <int N>
+__device__ __forceinline__ void group_sum(float (&acc)[N], int ls)
+{
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        if (ls > 0) acc[t] = dpp_add<0xB1>(acc[t]);   // lane ^ 1
+        if (ls > 1) acc[t] = dpp_add<0x4E>(acc[t]);   // lane ^ 2
+        if (ls > 2) acc[t] = dpp_add<0x141>(acc[t]);  // 7 - lane in 8: the other four
+        if (ls > 3) acc[t] = dpp_add<0x140>(acc[t]);  // 15 - lane in 16: the other eight
+        if (ls > 4) acc[t] += __shfl_xor(acc[t], 16, 64);
+        if (ls > 5) acc[t] += __shfl_xor(acc[t], 32, 64);
     }
 }
 
@@ -1207,20 +1254,33 @@ __device__ void tile_bounds(float (&bl)[7], float* __restrict__ shbox)
 // Forward sums over one staged chunk: keys k = ph, ph + Sf, ... against the
 // lane's query (Alg. 1 with the reference exponent M).
 template <int DEG>
+__device__ __forceinline__ void fwd_pair(const TileSmem<DEG>& S, int k, const float4 q, const float M, float& e, float& m)
+{
+    const float4 kc = S.kc[k], kv = S.kv[k];
+    const KeyQ<DEG> kq = load_q(S, k);
+    const float dx = q.x - kc.x, dy = q.y - kc.y, dz = q.z - kc.z;
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float l = ex2(fmaf(kc.w, r2, -M));
+    const float f = poly<DEG>(kv, kq, dx, dy, dz);
+    e += l;
+    m = fmaf(l, f, m);
+}
+
+template <int DEG>
 __device__ __forceinline__ void fwd_sums(const TileSmem<DEG>& S, int n, int ph, int Sf, const float4 q,
                                          const float M, float& e, float& m)
 {
-#pragma unroll 4
-    for (int k = ph; k < n; k += Sf) {
-        const float4 kc = S.kc[k], kv = S.kv[k];
-        const KeyQ<DEG> kq = load_q(S, k);
-        const float dx = q.x - kc.x, dy = q.y - kc.y, dz = q.z - kc.z;
-        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        const float l = ex2(fmaf(kc.w, r2, -M));
-        const float f = poly<DEG>(kv, kq, dx, dy, dz);
-        e += l;
-        m = fmaf(l, f, m);
+    if (Sf == 1) {  // the same keys for all lanes: no address arithmetic per key
+        int k = 0;
+        for (; k + 4 <= n; k += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) fwd_pair<DEG>(S, k + u, q, M, e, m);
+        }
+        for (; k < n; ++k) fwd_pair<DEG>(S, k, q, M, e, m);
+        return;
     }
+#pragma unroll 4
+    for (int k = ph; k < n; k += Sf) fwd_pair<DEG>(S, k, q, M, e, m);
 }
 
 template <int DEG>
@@ -1253,6 +1313,22 @@ __device__ __forceinline__ void fwd_qgrad(const TileSmem<DEG>& S, int n, int ph,
         gy += fmaf(w, fy, t * dy);
         gz += fmaf(w, fz, t * dz);
     }
+}
+
+// Largest logit of key kc against any point of the box; slack: relative error
+// of the centre's coordinates.
+__device__ __forceinline__ float box_logit(const float4 kc, const float (&bl)[7], float slack)
+{
+    const float dx = fmaxf(fmaxf(bl[0] - kc.x, kc.x - bl[3]) - slack * fabsf(kc.x), 0.0f);
+    const float dy = fmaxf(fmaxf(bl[1] - kc.y, kc.y - bl[4]) - slack * fabsf(kc.y), 0.0f);
+    const float dz = fmaxf(fmaxf(bl[2] - kc.z, kc.z - bl[5]) - slack * fabsf(kc.z), 0.0f);
+    return kc.w * fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+}
+
+// Set bits of m below this lane.
+__device__ __forceinline__ int bits_below(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
 // Pair counts of the tiles a workgroup has run (flushed to DevStats once).
@@ -1289,7 +1365,7 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 template <int MODE, bool QGRAD, int DEG>
 __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, const int4 td, const int2 whole,
                                          const int lanes, const int tile, const int W, const float bmin2, PairCount& pc,
-                                         const bool half_batches, const bool add_loss)
+                                         const bool add_loss)
 {
     static_assert(KC == BLOCK, "one staged key per thread");
     constexpr int GW = gk_width(DEG), MW = mk_width(DEG);
@@ -1317,7 +1393,6 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     const int nmy = my1 - my0 + 1;
     const int nrow = a.offsets ? (mx1 - mx0 + 1) * nmy : 0;
     const int ngroups = (nrow + MAXSEG - 1) / MAXSEG;
-    const int ngc = (Kg + KC - 1) / KC;
     // Tile origin.  A float32 subtraction rounds the exact difference of
     // two float32 coordinates once, so grid keys and queries are taken
     // relative to it in float32; moved centres (hi + lo) use double.
@@ -1334,52 +1409,53 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         S.pq[p] = make_float4(v.x - oxf, v.y - oyf, v.z - ozf, v.w);
         if (MODE == MODE_GRAD) {
             const float4 u = a.pv[p0 + p];
-            S.pv[p] = make_float4(u.x, u.y * LOG2E, v.w, 0.0f);
+            S.pv[p] = make_float2(u.x, u.y * LOG2E);
         }
     }
 
     // ---- candidate gathering
-    int ncand = 0;              // tags in S.cand
+    int lbase = 0, lend = 0;  // S.cand[lbase, lend): tags not yet loaded
+    bool logged = true;       // S.cand[0, lend) holds every tag since the pass began
     int grp = -1, grpK = 0, grpN = 0;  // moved-row group whose segment table is built
     struct Cursor {
-        int gc, gi, km;         // next grid chunk; moved-row group; next moved key in it
+        int gc, gi, km;         // next grid candidate; moved-row group; next moved key in it
     };
     // Segment table of moved-row group gi: rows [gi MAXSEG, ...) of the window.
     auto build_group = [&](int gi) {
+        static_assert(MAXSEG == BLOCK, "one row per thread");
         const int r0 = gi * MAXSEG, nr = min(MAXSEG, nrow - r0);
-        int Km = 0;
-        for (int base = 0; base < nr; base += BLOCK) {
-            const int s = base + tid;
-            int len = 0;
-            if (s < nr) {
-                const int r = r0 + s;
-                const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
-                const int src = a.mstart[row + mz0];
-                len = a.mstart[row + mz1 + 1] - src;
-                S.seg_src[s] = src;
-            }
-            int total;
-            const int ex = block_excl_scan(len, S.isc, &total);
-            if (s < nr) S.seg_off[s] = Km + ex;
-            Km += total;
+        int len = 0;
+        if (tid < nr) {
+            const int r = r0 + tid;
+            const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
+            const int src = a.mstart[row + mz0];
+            len = a.mstart[row + mz1 + 1] - src;
+            S.seg_src[tid] = src;
         }
+        int total;
+        const int ex = block_excl_scan(len, S.isc, &total);
+        if (tid < nr) S.seg_off[tid] = ex;
         grp = gi;
-        grpK = Km;
+        grpK = __builtin_amdgcn_readfirstlane(total);
         grpN = nr;
         __syncthreads();
     };
-    // Cull candidates [k0, k0 + nk) of the grid part (grid) or of the built
-    // moved-row group: keep those whose largest logit against any point of
-    // the box reaches cutoff (every dropped pair weighs below
+    // Cull candidates [k0, k0 + nk), nk <= 2 KC, of the grid part (grid) or of
+    // the built moved-row group: keep those whose largest logit against any
+    // point of the box reaches cutoff (every dropped pair weighs below
     // 2^(cutoff - lse2) <= e^-T) and append their tags: packed vertex
     // indices ix | iy << 9 | iz << 18 for grid keys, -(record + 1) for moved.
+    // Two candidates per thread: a pass waits for its loads and barriers
+    // (about 1 us with few tiles in flight), whatever it tests.
     unsigned long long ncull = 0ull;  // candidates tested (statistics)
     auto cull = [&](bool grid, int k0, int nk, const float (&bl)[7], float cutoff) {
         ncull += nk;
-        int tag = 0;
-        bool keep = false;
-        if (tid < nk) {
-            const int kk = k0 + tid;
+        int tag[2] = {0, 0};
+        bool keep[2] = {false, false};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (i * BLOCK + tid >= nk) continue;
+            const int kk = k0 + i * BLOCK + tid;
             float4 kc;
             float slack = 0.0f;
             if (grid) {
@@ -1395,7 +1471,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 const int vid = (ix * R + iy) * R + iz;
                 const float nb = reinterpret_cast<const float*>(a.gk)[4 * GW * (int64_t)vid];
                 kc = make_float4(g.tlat[ix] - oxf, g.tlat[iy] - oyf, g.tlat[iz] - ozf, nb);
-                tag = ix | (iy << 9) | (iz << 18);
+                tag[i] = ix | (iy << 9) | (iz << 18);
             } else {
                 int lo = 0, hi = grpN - 1;
                 while (lo < hi) {
@@ -1407,44 +1483,54 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 // float32 centre: within three roundoffs of the loaded one
                 kc = make_float4((b0.x - oxf) + b2.x, (b0.y - oyf) + b2.y, (b0.z - ozf) + b2.z, b0.w);
                 slack = U3;
-                tag = -(slot + 1);
+                tag[i] = -(slot + 1);
             }
-            const float dx = fmaxf(fmaxf(bl[0] - kc.x, kc.x - bl[3]) - slack * fabsf(kc.x), 0.0f);
-            const float dy = fmaxf(fmaxf(bl[1] - kc.y, kc.y - bl[4]) - slack * fabsf(kc.y), 0.0f);
-            const float dz = fmaxf(fmaxf(bl[2] - kc.z, kc.z - bl[5]) - slack * fabsf(kc.z), 0.0f);
-            keep = kc.w * fmaf(dx, dx, fmaf(dy, dy, dz * dz)) >= cutoff;
+            keep[i] = box_logit(kc, bl, slack) >= cutoff;
         }
-        // position among the kept: wave ballot, then the waves before
-        const unsigned long long bal = __ballot(keep);
-        const int lane = tid & 63, wv = tid >> 6;
+        // position among the kept: wave ballots, then the waves before
+        const int wv = tid >> 6;
+        const unsigned long long b0 = __ballot(keep[0]), b1 = __ballot(keep[1]);
         __syncthreads();
-        if (lane == 0) S.isc[wv] = __popcll(bal);
+        if ((tid & 63) == 0) {
+            S.isc[wv] = __popcll(b0);
+            S.isc[BLOCK / 64 + wv] = __popcll(b1);
+        }
         __syncthreads();
-        int before = 0, tot = 0;
+        int before[2] = {0, 0}, tot = 0;
 #pragma unroll
-        for (int i = 0; i < BLOCK / 64; ++i) {
+        for (int i = 0; i < 2 * (BLOCK / 64); ++i) {
             const int c = S.isc[i];
-            before += i < wv ? c : 0;
+            before[0] += i < wv ? c : 0;
+            before[1] += i < BLOCK / 64 + wv ? c : 0;
             tot += c;
         }
-        if (keep) S.cand[ncand + before + __popcll(bal & ((1ull << lane) - 1ull))] = tag;
-        ncand += tot;
+        if (keep[0]) S.cand[lend + before[0] + bits_below(b0)] = tag[0];
+        if (keep[1]) S.cand[lend + before[1] + bits_below(b1)] = tag[1];
+        lend += __builtin_amdgcn_readfirstlane(tot);
     };
-    // Cull chunks until lim (<= KC) tags have gathered or the window is
-    // exhausted.
+    // Cull until lim (<= KC) tags wait to be loaded or the window is exhausted.
     auto gather = [&](Cursor& cu, const float (&bl)[7], float cutoff, int lim) {
-        while (ncand < lim) {
-            if (cu.gc < ngc) {
-                const int k0 = cu.gc * KC;
-                cull(true, k0, min(KC, Kg - k0), bl, cutoff);
-                ++cu.gc;
+        while (lend - lbase < lim) {
+            if (cu.gc >= Kg && cu.gi >= ngroups) break;
+            if (lend + 2 * KC > LOGCAP) {  // move the waiting tags (< KC) to the front
+                const int n = lend - lbase;
+                __syncthreads();
+                const int t = tid < n ? S.cand[lbase + tid] : 0;
+                __syncthreads();
+                if (tid < n) S.cand[tid] = t;
+                lbase = 0;
+                lend = n;
+                logged = false;
+            }
+            if (cu.gc < Kg) {
+                cull(true, cu.gc, min(2 * KC, Kg - cu.gc), bl, cutoff);
+                cu.gc += 2 * KC;
                 continue;
             }
-            if (cu.gi >= ngroups) break;
             if (grp != cu.gi) build_group(cu.gi);
             if (cu.km < grpK) {
-                cull(false, cu.km, min(KC, grpK - cu.km), bl, cutoff);
-                cu.km += KC;
+                cull(false, cu.km, min(2 * KC, grpK - cu.km), bl, cutoff);
+                cu.km += 2 * KC;
             }
             if (cu.km >= grpK) {
                 ++cu.gi;
@@ -1452,54 +1538,86 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             }
         }
     };
-    // Load the first min(ncand, lim) gathered keys in full into slots
-    // [0, n) and keep the rest of the tags (fewer than KC) for the next
-    // batch; returns n and the number of moved keys among them.
-    auto load_batch = [&](int& nmoved, int lim) -> int {
-        const int n = min(ncand, lim), rem = ncand - n;
-        __syncthreads();  // tags complete; the previous batch is no longer read
-        const int t0 = tid < n ? S.cand[tid] : 0;
-        const int t1 = tid < rem ? S.cand[n + tid] : 0;
-        __syncthreads();
-        if (tid < rem) S.cand[tid] = t1;
-        ncand = rem;
-        if (tid < n) {
-            float4 kc, kv, q0 = make_float4(0, 0, 0, 0), q1 = make_float4(0, 0, 0, 0);
-            int kid;
-            if (t0 >= 0) {
-                const int ix = t0 & 511, iy = (t0 >> 9) & 511, iz = t0 >> 18;
-                const int vid = (ix * R + iy) * R + iz;
-                const float4 a0 = a.gk[GW * (int64_t)vid], a1 = a.gk[GW * (int64_t)vid + 1];
-                if (DEG == 2) {
-                    q0 = a.gk[GW * (int64_t)vid + 2];
-                    q1 = a.gk[GW * (int64_t)vid + 3];
-                }
-                kc = make_float4(g.tlat[ix] - oxf, g.tlat[iy] - oyf, g.tlat[iz] - ozf, a0.x);
-                kv = make_float4(a0.y, a0.z, a0.w, a1.x);
-                kid = vid;
-            } else {
-                const int64_t slot = -(int64_t)t0 - 1;
-                const float4 b0 = a.mk[MW * slot], b1 = a.mk[MW * slot + 1], b2 = a.mk[MW * slot + 2];
-                if (DEG == 2) {
-                    q0 = a.mk[MW * slot + 3];
-                    q1 = a.mk[MW * slot + 4];
-                }
-                kc = make_float4((float)(((double)b0.x - ox) + (double)b2.x),
-                                 (float)(((double)b0.y - oy) + (double)b2.y),
-                                 (float)(((double)b0.z - oz) + (double)b2.z), b0.w);
-                kv = b1;
-                kid = (int)(-slot - 1);  // the record: moved gradients accumulate by record
-            }
-            S.kc[tid] = kc;
-            S.kv[tid] = kv;
+    // The key of tag t in full, centre relative to the tile origin.
+    auto load_key = [&](int t, float4& kc, float4& kv, float4& q0, float2& q1) {
+        if (t >= 0) {
+            const int ix = t & 511, iy = (t >> 9) & 511, iz = t >> 18;
+            const int vid = (ix * R + iy) * R + iz;
+            const float4 a0 = a.gk[GW * (int64_t)vid], a1 = a.gk[GW * (int64_t)vid + 1];
             if (DEG == 2) {
-                S.kqa[tid] = q0;
-                S.kqb[tid] = make_float2(q1.x, q1.y);
+                q0 = a.gk[GW * (int64_t)vid + 2];
+                const float4 a3 = a.gk[GW * (int64_t)vid + 3];
+                q1 = make_float2(a3.x, a3.y);
             }
-            S.kid[tid] = kid;
+            kc = make_float4(g.tlat[ix] - oxf, g.tlat[iy] - oyf, g.tlat[iz] - ozf, a0.x);
+            kv = make_float4(a0.y, a0.z, a0.w, a1.x);
+        } else {
+            const int64_t slot = -(int64_t)t - 1;
+            const float4 b0 = a.mk[MW * slot], b1 = a.mk[MW * slot + 1], b2 = a.mk[MW * slot + 2];
+            if (DEG == 2) {
+                q0 = a.mk[MW * slot + 3];
+                const float4 a3 = a.mk[MW * slot + 4];
+                q1 = make_float2(a3.x, a3.y);
+            }
+            kc = make_float4((float)(((double)b0.x - ox) + (double)b2.x),
+                             (float)(((double)b0.y - oy) + (double)b2.y),
+                             (float)(((double)b0.z - oz) + (double)b2.z), b0.w);
+            kv = b1;
         }
-        nmoved = __syncthreads_count(tid < n && t0 < 0);
-        return n;
+    };
+    auto put_key = [&](int i, int t, const float4 kc, const float4 kv, const float4 q0, const float2 q1) {
+        S.kc[i] = kc;
+        S.kv[i] = kv;
+        if (DEG == 2) {
+            S.kqa[i] = q0;
+            S.kqb[i] = q1;
+        }
+        S.kid[i] = t;
+    };
+    // Load the keys of tags S.cand[b, b + n), n <= KC, in full into slots
+    // [0, n); returns the number of moved keys among them.
+    auto load_batch = [&](int b, int n) -> int {
+        __syncthreads();  // tags complete; the previous batch is no longer read
+        const int t0 = tid < n ? S.cand[b + tid] : 0;
+        if (tid < n) {
+            float4 kc, kv, q0;
+            float2 q1;
+            load_key(t0, kc, kv, q0, q1);
+            put_key(tid, t0, kc, kv, q0, q1);
+        }
+        return __builtin_amdgcn_readfirstlane(__syncthreads_count(tid < n && t0 < 0));
+    };
+    // The same for those of the n tags whose keys reach the box, compacted;
+    // returns their number.
+    auto load_kept = [&](int b, int n, const float (&bl)[7], float cutoff, int& nmoved) -> int {
+        const int t0 = tid < n ? S.cand[b + tid] : 0;
+        float4 kc, kv, q0;
+        float2 q1;
+        bool keep = false;
+        if (tid < n) {
+            load_key(t0, kc, kv, q0, q1);
+            keep = box_logit(kc, bl, 0.0f) >= cutoff;
+        }
+        const int wv = tid >> 6;
+        const unsigned long long b0 = __ballot(keep), bm = __ballot(keep && t0 < 0);
+        __syncthreads();  // the previous batch is no longer read
+        if ((tid & 63) == 0) {
+            S.isc[wv] = __popcll(b0);
+            S.isc[BLOCK / 64 + wv] = __popcll(bm);
+        }
+        __syncthreads();
+        int before = 0, tot = 0, mv = 0;
+#pragma unroll
+        for (int i = 0; i < BLOCK / 64; ++i) {
+            const int c = S.isc[i];
+            before += i < wv ? c : 0;
+            tot += c;
+            mv += S.isc[BLOCK / 64 + i];
+        }
+        if (keep) put_key(before + bits_below(b0), t0, kc, kv, q0, q1);
+        __syncthreads();
+        nmoved = __builtin_amdgcn_readfirstlane(mv);
+        return __builtin_amdgcn_readfirstlane(tot);
     };
 
     // moved keys in the window (all row groups); group 0's table stays built
@@ -1519,7 +1637,6 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     }
 
     unsigned long long fwd_pairs = 0ull, fwd_moved = 0ull;
-    int kept_f = 0;  // keys the forward kept (0 without a forward)
 
     if (MODE != MODE_GRAD) {
         __syncthreads();
@@ -1551,7 +1668,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             }
             // exp2(s - M0) <= 2^-M0 per key; keep the sum of K such terms finite
             if (!(-M0 + log2f((float)Kg + (float)Kmt + 1.0f) < 120.0f)) need_exact = 1;
-            if (own) S.pv[p] = make_float4(0.0f, 0.0f, 0.0f, M0);
+            if (own) S.pv[p] = make_float2(0.0f, M0);
             if (!own && lanes) continue;
             bl[0] = fminf(bl[0], x); bl[1] = fminf(bl[1], y); bl[2] = fminf(bl[2], z);
             bl[3] = fmaxf(bl[3], x); bl[4] = fmaxf(bl[4], y); bl[5] = fmaxf(bl[5], z);
@@ -1582,23 +1699,25 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             // no grid keys to take the reference from)
             float M = -INFINITY, M2 = -INFINITY;
             Cursor cu = {0, 0, 0};
-            ncand = 0;
             for (;;) {
                 gather(cu, bl, fcut, KC);
-                if (ncand == 0) break;
-                int nm;
-                const int n = load_batch(nm, KC);
+                const int n = min(lend - lbase, KC);
+                if (n == 0) break;
+                load_batch(lbase, n);
+                lbase += n;
                 if (act) fwd_max<DEG>(S, n, ph, Sf, q, M);
                 if (act2) fwd_max<DEG>(S, n, ph2, Sf2, q2, M2);
             }
+            lbase = lend = 0;
+            logged = true;
             S.red[tid].x = M;
             S.red[BLOCK + tid].x = M2;
             __syncthreads();
             float mn = INFINITY;
             for (int p = tid; p < P; p += BLOCK) {
-                float mx = S.pv[p].w;
+                float mx = S.pv[p].y;
                 for (int s = 0; s < nslot(p); ++s) mx = fmaxf(mx, S.red[slot0(p) + s].x);
-                S.pv[p].w = mx;
+                S.pv[p].y = mx;
                 mn = fminf(mn, mx);
             }
             // the exact maxima are tighter lower bounds of lse2
@@ -1608,20 +1727,19 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         // ---- forward: e = sum 2^(s - M), m = sum 2^(s - M) f   (Alg. 1)
         float e = 0.0f, m = 0.0f, e2 = 0.0f, m2 = 0.0f;
         __syncthreads();
-        const float Mr = S.pv[act ? pme : 0].w;
-        const float Mr2 = S.pv[act2 ? BLOCK + pme2 : 0].w;
+        const float Mr = S.pv[act ? pme : 0].y;
+        const float Mr2 = S.pv[act2 ? BLOCK + pme2 : 0].y;
         {
             Cursor cu = {0, 0, 0};
-            ncand = 0;
             for (;;) {
                 gather(cu, bl, fcut, KC);
-                if (ncand == 0) break;
-                int nm;
-                const int n = load_batch(nm, KC);
-                fwd_pairs += (unsigned long long)n * P;
-                fwd_moved += (unsigned long long)nm * P;
+                const int n = min(lend - lbase, KC);
+                if (n == 0) break;
+                const int nm = load_batch(lbase, n);
+                lbase += n;
+                fwd_pairs += (unsigned)(n * P);
+                fwd_moved += (unsigned)(nm * P);
                 pc.kept += n;
-                kept_f += n;
                 if (act) fwd_sums<DEG>(S, n, ph, Sf, q, Mr, e, m);
                 if (act2) fwd_sums<DEG>(S, n, ph2, Sf2, q2, Mr2, e2, m2);
             }
@@ -1649,7 +1767,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 mm += r.y;
             }
             const float4 pq = S.pq[p];
-            const float M = S.pv[p].w;
+            const float M = S.pv[p].y;
             const float O = mm / ee;
             const float lse2 = M + log2f(ee);
             float D = fminf(fminf(pq.x - flx, fhx - pq.x),
@@ -1668,15 +1786,17 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                     lsq += (double)res * (double)res;
                     lab += fabs((double)res);
                 }
-                S.pv[p] = make_float4(O, lse2, gj, M);
+                S.pq[p].w = gj;
             } else {  // EVAL
                 if (cert) {
                     const int j = a.pidx[p0 + p];
                     a.O_out[j] = O;
                     if (a.lse_out) a.lse_out[j] = lse2 * LN2;
                 }
-                S.pv[p] = make_float4(O, lse2, cert ? 1.0f : 0.0f, M);
+                S.pq[p].w = cert ? 1.0f : 0.0f;
             }
+            // an uncertified query's pairs weigh 0 in the backward
+            S.pv[p] = MODE != MODE_FIT || cert ? make_float2(O, lse2) : make_float2(0.0f, INFINITY);
         }
         if (MODE == MODE_FIT) {
             lsq = block_sum(lsq, S.dsc);
@@ -1696,30 +1816,41 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             const float O1 = S.pv[act ? pme : 0].x, L1 = S.pv[act ? pme : 0].y;
             const float O2 = S.pv[act2 ? BLOCK + pme2 : 0].x, L2 = S.pv[act2 ? BLOCK + pme2 : 0].y;
             float gx = 0, gy = 0, gz = 0, hx = 0, hy = 0, hz = 0;
+            // the forward's keys once more: from their tags if all are at hand
+            const bool replay = logged;
+            const int total = lend;
             Cursor cu = {0, 0, 0};
-            ncand = 0;
+            int b = 0;
+            if (!replay) lbase = lend = 0;
             for (;;) {
-                gather(cu, bl, fcut, KC);
-                if (ncand == 0) break;
-                int nm;
-                const int n = load_batch(nm, KC);
+                int n;
+                if (replay) {
+                    n = min(total - b, KC);
+                } else {
+                    gather(cu, bl, fcut, KC);
+                    b = lbase;
+                    n = min(lend - lbase, KC);
+                    lbase += n;
+                }
+                if (n == 0) break;
+                load_batch(b, n);
+                b += n;
                 if (act) fwd_qgrad<DEG>(S, n, ph, Sf, q, O1, L1, gx, gy, gz);
                 if (act2) fwd_qgrad<DEG>(S, n, ph2, Sf2, q2, O2, L2, hx, hy, hz);
             }
             __syncthreads();
-            float* zf = S.fv;  // keys no longer needed
             S.red[tid] = make_float2(gx, gy);
-            zf[tid] = gz;
+            S.redz[tid] = gz;
             S.red[BLOCK + tid] = make_float2(hx, hy);
-            zf[BLOCK + tid] = hz;
+            S.redz[BLOCK + tid] = hz;
             __syncthreads();
             for (int p = tid; p < P; p += BLOCK) {
-                if (S.pv[p].z == 0.0f) continue;  // uncertified: fallback writes it
+                if (S.pq[p].w == 0.0f) continue;  // uncertified: fallback writes it
                 float sx = 0.0f, sy = 0.0f, sz = 0.0f;
                 for (int s = 0; s < nslot(p); ++s) {
                     sx += S.red[slot0(p) + s].x;
                     sy += S.red[slot0(p) + s].y;
-                    sz += zf[slot0(p) + s];
+                    sz += S.redz[slot0(p) + s];
                 }
                 const int j = a.pidx[p0 + p];
                 a.dOdq_out[3 * (int64_t)j] = sx;
@@ -1738,16 +1869,14 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         const float fhz = (cz1 + W < R - 1) ? g.tlat[cz1 + W + 1] - ozf : INFINITY;
         for (int p = tid; p < P; p += BLOCK) {
             const float4 pq = S.pq[p];
-            float4 pv = S.pv[p];
             float D = fminf(fminf(pq.x - flx, fhx - pq.x),
                             fminf(fminf(pq.y - fly, fhy - pq.y), fminf(pq.z - flz, fhz - pq.z)));
             D = fmaxf(D * (1.0f - 1e-5f) - 1e-6f * g.h, 0.0f);
-            const bool cert = bmin2 * D * D >= a.T2 - pv.y;
+            const bool cert = bmin2 * D * D >= a.T2 - S.pv[p].y;
             if (!cert) {
                 const int slot = atomicAdd(&a.st->nfb, 1);
                 a.fb[slot] = p0 + p;
-                pv.z = 0.0f;
-                S.pv[p] = pv;
+                S.pq[p].w = 0.0f;
             }
         }
     }
@@ -1760,138 +1889,135 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         float bl[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, INFINITY};
         __syncthreads();
         for (int p = tid; p < P; p += BLOCK) {
-            const float4 pv = S.pv[p];
-            if (pv.z == 0.0f) continue;
             const float4 pq = S.pq[p];
+            if (pq.w == 0.0f) continue;
             bl[0] = fminf(bl[0], pq.x); bl[1] = fminf(bl[1], pq.y); bl[2] = fminf(bl[2], pq.z);
             bl[3] = fmaxf(bl[3], pq.x); bl[4] = fmaxf(bl[4], pq.y); bl[5] = fmaxf(bl[5], pq.z);
-            bl[6] = fminf(bl[6], pv.y);
+            bl[6] = fminf(bl[6], S.pv[p].y);
         }
         tile_bounds(bl, &S.box[0][0]);
         const float bcut = bl[6] - a.T2;
+        constexpr int NA = NAcc<DEG>::n;
+        constexpr int NF = TileSmem<DEG>::NF, FS = TileSmem<DEG>::FS;
+        constexpr int NV = DEG == 0 ? 1 : (DEG == 1 ? 4 : 10);
+        // this thread's flush slot, its channel of grid and of moved keys
+        const int sl = tid % NF;
+        const int cg = sl < NV ? L.gval + sl : (sl == NV ? L.grho : -1);
+        const int cm = sl < 3 ? L.mdel + sl : (sl < 3 + NV ? L.mval + (sl - 3) : (sl == 3 + NV ? L.mrho : -1));
 
-        // Batches of at most kb keys.  The last batch of a tile holds the
-        // remainder; with kb = 128 every full batch gives each key 2 lanes
-        // (half the queries each) and a remainder of at most 64 keys 4, so
-        // a tile with a few hundred kept keys leaves fewer lanes of its
-        // last, partly filled wave idle than with batches of 256 (one lane
-        // per key).  Tiles whose forward kept more than 512 keys keep 256:
-        // their remainder is one batch among several, and the extra batches
-        // cost more than the idle lanes; so do tiles with few queries.
-        // Without a forward (gradient calls) the window decides.  The
-        // batched kernel keeps 256 throughout: it spills registers, and
-        // every extra batch reloads them (measured 7 % slower over the
-        // 64-shape batch with half batches, 1.6 % faster at 32^3 here).
-        const int kb = half_batches && P >= 192 && (MODE == MODE_GRAD ? Kg + Kmt <= 1024 : kept_f <= 512)
-                           ? KC / 2 : KC;
+        // The forward's keys that reach these queries: from the forward's
+        // tags if S.cand still holds them all (the backward's cut is the
+        // sharper one), else from the window.
+        const bool replay = MODE == MODE_FIT && logged;
+        const int total = lend;
         Cursor cu = {0, 0, 0};
-        ncand = 0;
+        int b = 0;
+        if (!replay) lbase = lend = 0;
         for (;;) {
-            gather(cu, bl, bcut, kb);
-            if (ncand == 0) break;
-            int nmv;
-            const int n = load_batch(nmv, kb);
-            bwd_pairs += (unsigned long long)n * P;
-            bwd_moved += (unsigned long long)nmv * P;
-            int Sb = 1;
-            while (Sb < 64 && Sb * 2 * n <= BLOCK) Sb *= 2;
-            const int kk = tid / Sb, ph = tid - kk * Sb;
-            const bool act = kk < n;
-            constexpr int NA = NAcc<DEG>::n;
-            constexpr int NF = TileSmem<DEG>::NF;
-            constexpr int NV = DEG == 0 ? 1 : (DEG == 1 ? 4 : 10);
-            float acc[NA];
-#pragma unroll
-            for (int t = 0; t < NA; ++t) acc[t] = 0.0f;
-            float4 kc = make_float4(0, 0, 0, 0), kv = make_float4(0, 0, 0, 0);
-            KeyQ<DEG> kq;
-            int tag = 0;
-            if (act) {
-                kc = S.kc[kk];
-                kv = S.kv[kk];
-                kq = load_q(S, kk);
-                tag = S.kid[kk];
-            }
-            const bool moved = act && tag < 0;
-            if (__any(moved)) {
-                if (act) bwd_key<true, DEG>(S, P, ph, Sb, kc, kv, kq, acc);
+            int n, nmv;
+            if (replay) {
+                if (b >= total) break;
+                n = min(total - b, KC);
+                b += n;
+                n = load_kept(b - n, n, bl, bcut, nmv);
             } else {
-                if (act) bwd_key<false, DEG>(S, P, ph, Sb, kc, kv, kq, acc);
+                gather(cu, bl, bcut, KC);
+                n = min(lend - lbase, KC);
+                if (n == 0) break;
+                nmv = load_batch(lbase, n);
+                lbase += n;
             }
-            for (int off = 1; off < Sb; off <<= 1) {
+            bwd_pairs += (unsigned)(n * P);
+            bwd_moved += (unsigned)(nmv * P);
+            // The batch's keys in parts of 256, 128, ... keys with 1, 2, ...
+            // lanes each (a lane takes every 2nd, ... query), so that a
+            // remainder does not leave lanes idle; with few queries in one
+            // part, whose other costs then weigh more.
+            for (int k0 = 0; k0 < n;) {
+                const int rem = n - k0;
+                int ls = 0;
+                if (P >= 64)
+                    while (ls < 4 && rem <= (3 * (BLOCK / 4)) >> ls) ++ls;
+                else
+                    while (ls < 6 && rem << (ls + 1) <= BLOCK) ++ls;
+                const int kk = k0 + (tid >> ls), ph = tid & ((1 << ls) - 1);
+                const bool act = kk < n;
+                const int kr = act ? kk : n - 1;
+                const float4 kc = S.kc[kr], kv = S.kv[kr];
+                const KeyQ<DEG> kq = load_q(S, kr);
+                const bool moved = act && S.kid[kr] < 0;
+                float acc[NA];
 #pragma unroll
-                for (int t = 0; t < NA; ++t) acc[t] += __shfl_xor(acc[t], off, 64);
-            }
-            // Final channel values (Sec. 3.6).  Grid key: values (nv), rho.
-            // Moved key: Delta = centre gradient, values (nv), rho'.
-            // dL/dv = sum delta * monomial; dL/drho = beta dL/dbeta =
-            // -beta sum u |x|^2; dL/dc = -sum delta grad_x f + 2 beta sum u x
-            // with sum delta grad_x f = d sum delta + S sum delta x.
-            const float beta = -kc.w * LN2;
-            float val[NF];
-#pragma unroll
-            for (int t = 0; t < NF; ++t) val[t] = 0.0f;
-            const int vo = moved ? 3 : 0;
-            val[vo] = acc[0];
-            if (DEG >= 1) {
-                val[vo + 1] = acc[1];
-                val[vo + 2] = acc[2];
-                val[vo + 3] = acc[3];
-            }
-            if (DEG == 2) {
-#pragma unroll
-                for (int t = 0; t < 6; ++t) val[vo + 4 + t] = acc[8 + t];
-            }
-            val[vo + NV] = -beta * acc[4];
-            if (moved) {
-                float gx = 2.0f * beta * acc[5], gy = 2.0f * beta * acc[6], gz = 2.0f * beta * acc[7];
-                if constexpr (DEG >= 1) {
-                    gx = fmaf(-kv.y, acc[0], gx);
-                    gy = fmaf(-kv.z, acc[0], gy);
-                    gz = fmaf(-kv.w, acc[0], gz);
+                for (int t = 0; t < NA; ++t) acc[t] = 0.0f;
+                if (__any(act)) {
+                    if (__any(moved)) {
+                        if (ls == 0) bwd_key<true, 1, DEG>(S, P, ph, 1, kc, kv, kq, acc);
+                        else if (ls == 1) bwd_key<true, 2, DEG>(S, P, ph, 2, kc, kv, kq, acc);
+                        else bwd_key<true, 0, DEG>(S, P, ph, 1 << ls, kc, kv, kq, acc);
+                    } else {
+                        if (ls == 0) bwd_key<false, 1, DEG>(S, P, ph, 1, kc, kv, kq, acc);
+                        else if (ls == 1) bwd_key<false, 2, DEG>(S, P, ph, 2, kc, kv, kq, acc);
+                        else bwd_key<false, 0, DEG>(S, P, ph, 1 << ls, kc, kv, kq, acc);
+                    }
+                    group_sum(acc, ls);
                 }
-                if constexpr (DEG == 2) {  // - S sum(delta x)
-                    gx -= fmaf(2.0f * kq.a.x, acc[1], fmaf(kq.a.w, acc[2], kq.b.x * acc[3]));
-                    gy -= fmaf(kq.a.w, acc[1], fmaf(2.0f * kq.a.y, acc[2], kq.b.y * acc[3]));
-                    gz -= fmaf(kq.b.x, acc[1], fmaf(kq.b.y, acc[2], 2.0f * kq.a.z * acc[3]));
-                }
-                val[0] = gx;
-                val[1] = gy;
-                val[2] = gz;
-            }
-            __syncthreads();  // staged keys no longer needed: reuse their LDS
-            if (act && ph == 0) {
+                // Final channel values (Sec. 3.6).  Grid key: values (nv), rho.
+                // Moved key: Delta = centre gradient, values (nv), rho'.
+                // dL/dv = sum delta * monomial; dL/drho = beta dL/dbeta =
+                // -beta sum u |x|^2; dL/dc = -sum delta grad_x f + 2 beta sum u x
+                // with sum delta grad_x f = d sum delta + S sum delta x.
+                if (act && ph == 0) {
+                    const float beta = -kc.w * LN2;
+                    float* f = S.fv + kk;
+                    const int vo = moved ? 3 : 0;
+                    f[vo * FS] = acc[0];
+                    if (DEG >= 1) {
+                        f[(vo + 1) * FS] = acc[1];
+                        f[(vo + 2) * FS] = acc[2];
+                        f[(vo + 3) * FS] = acc[3];
+                    }
+                    if constexpr (DEG == 2) {
 #pragma unroll
-                for (int t = 0; t < NF; ++t) S.fv[kk * NF + t] = val[t];
+                        for (int t = 0; t < 6; ++t) f[(vo + 4 + t) * FS] = acc[8 + t];
+                    }
+                    f[(vo + NV) * FS] = -beta * acc[4];
+                    if (moved) {
+                        float gx = 2.0f * beta * acc[5], gy = 2.0f * beta * acc[6], gz = 2.0f * beta * acc[7];
+                        if constexpr (DEG >= 1) {
+                            gx = fmaf(-kv.y, acc[0], gx);
+                            gy = fmaf(-kv.z, acc[0], gy);
+                            gz = fmaf(-kv.w, acc[0], gz);
+                        }
+                        if constexpr (DEG == 2) {  // - S sum(delta x)
+                            gx -= fmaf(2.0f * kq.a.x, acc[1], fmaf(kq.a.w, acc[2], kq.b.x * acc[3]));
+                            gy -= fmaf(kq.a.w, acc[1], fmaf(2.0f * kq.a.y, acc[2], kq.b.y * acc[3]));
+                            gz -= fmaf(kq.b.x, acc[1], fmaf(kq.b.y, acc[2], 2.0f * kq.a.z * acc[3]));
+                        }
+                        f[0] = gx;
+                        f[FS] = gy;
+                        f[2 * FS] = gz;
+                    }
+                }
+                k0 += BLOCK >> ls;
             }
             __syncthreads();
             // one atomic per key channel, NF consecutive lanes per key
-            for (int t = tid; t < n * NF; t += BLOCK) {
-                const int kq2 = t / NF, sl = t - kq2 * NF;
-                const int tg = S.kid[kq2];
+            for (int kf = tid / NF; kf < n; kf += BLOCK / NF) {
+                const int tg = S.kid[kf];
                 const bool mv = tg < 0;
-                const float x = S.fv[t];
-                int c = -1;
-                if (!mv) {
-                    c = sl < NV ? L.gval + sl : (sl == NV ? L.grho : -1);
+                const int c = mv ? cm : cg;
+                if (c < 0) continue;
+                const float x = S.fv[sl * FS + kf];
+                if (x == 0.0f) continue;
+                const int64_t rec = mv ? -tg - 1 : ((tg & 511) * R + ((tg >> 9) & 511)) * R + (tg >> 18);
+                if (a.gfix) {
+                    // fixed point by vertex (the moved record carries its vertex)
+                    const int64_t v = mv ? (int64_t)__float_as_int(a.mk[MW * rec + 2].w) : rec;
+                    atomicAdd(a.gfix + v * L.nch + c, fixq(x, a.det->dscale[c]));
                 } else {
-                    c = sl < 3 ? L.mdel + sl
-                               : (sl < 3 + NV ? L.mval + (sl - 3) : (sl == 3 + NV ? L.mrho : -1));
-                }
-                if (c >= 0 && x != 0.0f) {
-                    if (a.gfix) {
-                        // fixed point by vertex (the moved record carries its vertex)
-                        const int64_t v = mv ? (int64_t)__float_as_int(a.mk[MW * (int64_t)(-tg - 1) + 2].w)
-                                             : (int64_t)tg;
-                        atomicAdd(a.gfix + v * L.nch + c, fixq(x, a.det->dscale[c]));
-                    } else if (mv) {
-                        // consecutive kept moved keys are consecutive records:
-                        // their slots share cache lines
-                        unsafeAtomicAdd(a.gslot + (int64_t)(-tg - 1) * NF + sl, x);
-                    } else {
-                        // grid key: its vertex's record (slot = channel)
-                        unsafeAtomicAdd(a.gslotg + (int64_t)tg * NF + sl, x);
-                    }
+                    // consecutive kept moved keys are consecutive records: their
+                    // slots share cache lines; a grid key has its vertex's record
+                    unsafeAtomicAdd((mv ? a.gslot : a.gslotg) + rec * NF + sl, x);
                 }
             }
         }
@@ -2030,7 +2156,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
         const int2 whole = make_int2(td.y, td.z);
         if (take_piece<MODE>(td, j, k, lanes))
             tile_run<MODE, QGRAD, DEG>(a, S, td, MODE == MODE_FIT ? whole : make_int2(td.y, td.z), lanes, item, W, bmin2,
-                                       pc, true, false);
+                                       pc, false);
         else if (MODE == MODE_FIT && threadIdx.x == 0)
             a.lpart[item] = make_double2(0.0, 0.0);
     }
@@ -2087,7 +2213,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
         if (!take_piece<MODE_FIT>(td, __builtin_amdgcn_readfirstlane(j), __builtin_amdgcn_readfirstlane(k), lanes))
             continue;
         tile_run<MODE_FIT, false, DEG>(a, S, td, whole, lanes, lt, __builtin_amdgcn_readfirstlane(a.st->W),
-                                       __uint_as_float(a.st->bmin_bits) * LOG2E, pc, false, true);
+                                       __uint_as_float(a.st->bmin_bits) * LOG2E, pc, true);
     }
     if (cur >= 0) flush_pairs(tab[cur].st, pc);
 }
