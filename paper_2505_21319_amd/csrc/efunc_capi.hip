@@ -360,13 +360,13 @@ int fit_step_impl(efunc_ctx* ctx, float* theta, float* m, float* v, int64_t step
     const bool slots = !ctx->w.det;
     p.defer_slots = slots ? 1 : 0;
     hipError_t e = run_tiles(ctx->w, p, MODE_FIT, s);
-    if (e == hipSuccess && loss_out) e = run_loss_finalize(ctx->w, J, loss_out, s);
+    if (e == hipSuccess && loss_out && !slots) e = run_loss_finalize(ctx->w, J, loss_out, s);
     if (e != hipSuccess) return hip_fail(e, "fit_step launch");
     const double bc1 = 1.0 - pow((double)hp.beta1, (double)step);
     const double bc2 = 1.0 - pow((double)hp.beta2, (double)step);
     if (slots)
         e = run_adam_fit(ctx->w, ctx->layout, theta, m, v, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay,
-                         (float)bc1, (float)bc2, s);
+                         (float)bc1, (float)bc2, J, loss_out, s);
     else
         e = run_adam(ctx->w, theta, m, v, (int64_t)ctx->layout.nch * ctx->w.I, hp.lr, hp.beta1, hp.beta2, hp.eps,
                      hp.weight_decay, (float)bc1, (float)bc2, s);
@@ -613,8 +613,8 @@ int efunc_eval(efunc_ctx* ctx, const float* theta, const float* q, int64_t J, fl
     p.lse_out = lse;
     p.dOdq_out = dOdq;
     p.grad = ctx->w.grad;
+    p.n_uncertified = n_uncertified;
     hipError_t e = run_tiles(ctx->w, p, MODE_EVAL, s);
-    if (e == hipSuccess && n_uncertified) e = run_count_uncertified(ctx->w, n_uncertified, s);
     if (e != hipSuccess) return hip_fail(e, "eval launch");
     return EFUNC_OK;
 }

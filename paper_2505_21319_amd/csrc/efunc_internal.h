@@ -130,7 +130,7 @@ struct Work {
     float4* mk;           // [mk_width I]  moved key records binned by cell
     int* pcell;           // [max_points] sort key of each query
     int* prank;           // [max_points]
-    int* pcount;          // [NK*PSPLIT] queries per (cell, sub-counter), block-major order
+    int* pcount;          // [NK*PSPLIT] queries per (cell, sub-counter) or, binned in LDS, [NK] per cell; block-major order
     int* pstart;          // [NK*PSPLIT+1]
     int* hist;            // [lnw NK] per-workgroup query counts per sort key (NK <= LBIN_MAX), else null
     int lnw;              // rows of hist
@@ -189,6 +189,7 @@ struct Problem {
     float* O_out;       // EVAL
     float* lse_out;     // EVAL (optional)
     float* dOdq_out;    // EVAL (optional)
+    int64_t* n_uncertified;  // queries evaluated against all keys (optional)
     float* grad;        // FIT: internal; GRAD: caller's (accumulated)
     // optional events recorded around the tile kernel
     hipEvent_t ev_start, ev_stop;
@@ -218,6 +219,7 @@ struct TileArgs {
     float* O_out;
     float* lse_out;
     float* dOdq_out;
+    int64_t* n_uncertified;
     float* grad;
     float* gslot;  // moved keys' gradient by binned record (see Work)
     float* gslotg; // grid keys' gradient by vertex (see Work)
@@ -274,20 +276,20 @@ hipError_t run_adam(const Work& w, float* theta, float* m, float* v, int64_t n, 
                     float beta1, float beta2, float eps, float wd, float bc1, float bc2,
                     hipStream_t s);
 // AdamW of the fit step on theta [I][nch], each channel's gradient taken
-// from grad plus its key's record slot in gslotg / gslot (all cleared).
+// from grad plus its key's record slot in gslotg / gslot (all cleared); the
+// loss of the J queries into loss_out (optional).
 hipError_t run_adam_fit(const Work& w, const Layout& L, float* theta, float* m, float* v, float lr,
-                        float beta1, float beta2, float eps, float wd, float bc1, float bc2, hipStream_t s);
+                        float beta1, float beta2, float eps, float wd, float bc1, float bc2, int64_t J,
+                        double* loss_out, hipStream_t s);
 hipError_t run_init_params(const Work& w, const Geo& g, const Layout& L, float* theta,
                            const float* surf, int64_t Ns, float bandwidth, float rho0,
                            hipStream_t s);
-hipError_t run_count_uncertified(const Work& w, int64_t* out, hipStream_t s);
 hipError_t run_zero_floats(float* p, int64_t n, hipStream_t s);
 // Flush slots per key of the tile kernel's backward (moved keys' gradient
 // records in gslot): 8, or 16 for degree 2.
 __host__ __device__ constexpr int flush_slots(int deg) { return deg == 2 ? 16 : 8; }
-// Adds the moved keys' gradient records (gslot, binned order) to grad
-// (vertex order) and clears them; batched form: one per shape of tab.
-hipError_t run_slot_finalize(const TileArgs& a, hipStream_t s);
+// Adds the keys' gradient records to grad and clears them.
+hipError_t run_slot_finalize(const Work& w, const Layout& L, float* grad, hipStream_t s);
 // Writes the R float32 vertex coordinates of [lo, hi] into t (one workgroup).
 hipError_t run_lattice(float* t, int R, double lo, double hi, hipStream_t s);
 

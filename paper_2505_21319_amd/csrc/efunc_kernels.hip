@@ -116,14 +116,17 @@ __global__ void k_fill_float(float* __restrict__ p, int64_t n)
         p[i] = 0.0f;
 }
 
-// Resets the statistics and zeroes a[0, na) and b[0, nb) (grid-stride).
-__global__ void k_reset_front(DevStats* st, int* __restrict__ a, int64_t na, int* __restrict__ b, int64_t nb)
+// Resets the statistics and the tile count and zeroes a[0, na) and b[0, nb)
+// (grid-stride).
+__global__ void k_reset_front(DevStats* st, int* __restrict__ ntiles, int* __restrict__ a, int64_t na,
+                              int* __restrict__ b, int64_t nb)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < na; i += (int64_t)gridDim.x * blockDim.x)
         a[i] = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nb; i += (int64_t)gridDim.x * blockDim.x)
         b[i] = 0;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
+        *ntiles = 0;
         st->bmin_bits = 0x7f800000u;  // +inf
         st->bgmax_bits = 0u;
         st->W = 1;
@@ -538,9 +541,8 @@ __global__ __launch_bounds__(BLOCK) void k_prep_keys(
 // Window half-width from the scale statistics: the smallest W >= 1 with
 // beta_min (W h)^2 >= T + beta_grid_max (3/4) h^2, so that every query inside
 // the lattice passes its certificate (its nearest vertex is within sqrt(3)/2 h).
-__global__ void k_window(DevStats* st, Geo g, float T, int Wforce)
+__device__ __forceinline__ void set_window(DevStats* __restrict__ st, const Geo& g, float T, int Wforce)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     int W;
     if (Wforce > 0) {
         W = Wforce;
@@ -683,10 +685,13 @@ __device__ __forceinline__ int order_key(int cx, int cy, int cz, int NB)
            (cz & 1);
 }
 
+// Both counting kernels run after the key preparation and set the window.
 __global__ void k_count_points(const float* __restrict__ q, int64_t J, Geo g, int* __restrict__ pcell,
-                               int* __restrict__ prank, int* __restrict__ pcount)
+                               int* __restrict__ prank, int* __restrict__ pcount, DevStats* __restrict__ st, float T,
+                               int Wforce)
 {
     const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (j == 0) set_window(st, g, T, Wforce);
     if (j >= J) return;
     // PSPLIT sub-counters per cell spread same-address atomics of dense cells
     const int c = order_key(cell_of(q[3 * j], g), cell_of(q[3 * j + 1], g), cell_of(q[3 * j + 2], g), g.NB) *
@@ -705,9 +710,11 @@ __global__ __launch_bounds__(LBIN_BLOCK) void k_count_points_lds(const float* __
                                                                   int64_t chunk, Geo g, int NK,
                                                                   int* __restrict__ pcell,
                                                                   int* __restrict__ prank,
-                                                                  int* __restrict__ hist)
+                                                                  int* __restrict__ hist,
+                                                                  DevStats* __restrict__ st, float T, int Wforce)
 {
     __shared__ int h[LBIN_MAX];
+    if (blockIdx.x == 0 && threadIdx.x == 0) set_window(st, g, T, Wforce);
     for (int i = threadIdx.x; i < NK; i += LBIN_BLOCK) h[i] = 0;
     __syncthreads();
     const int64_t j0 = blockIdx.x * chunk;
@@ -729,7 +736,7 @@ __global__ __launch_bounds__(LBIN_BLOCK) void k_count_points_lds(const float* __
             const int64_t j = jb + u * LBIN_BLOCK;
             const int r = atomicAdd(&h[key[u]], j < j1 ? 1 : 0);
             if (j < j1) {
-                pcell[j] = key[u] * PSPLIT;
+                pcell[j] = key[u];
                 prank[j] = r;
             }
         }
@@ -740,13 +747,10 @@ __global__ __launch_bounds__(LBIN_BLOCK) void k_count_points_lds(const float* __
 }
 
 // Per sort key: hist's column becomes its exclusive prefix over the
-// workgroups (in place), and the key's total goes to sub-counter 0 of pcount
-// with the other sub-counters zero, so the scan of pcount yields the same
-// cell starts as the atomic binning.  Loads are issued 16 rows at a time
-// ahead of the stores.
+// workgroups (in place), and the key's total goes to pcount.  Loads are issued
+// 16 rows at a time ahead of the stores.
 __global__ void k_hist_prefix(int* __restrict__ hist, int nw, int NK, int* __restrict__ pcount)
 {
-    static_assert(PSPLIT == 8, "two int4 stores per key");
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= NK) return;
     int s = 0;
@@ -760,9 +764,7 @@ __global__ void k_hist_prefix(int* __restrict__ hist, int nw, int NK, int* __res
             s += v[i];
         }
     }
-    int4* pc = reinterpret_cast<int4*>(pcount + (int64_t)k * PSPLIT);
-    pc[0] = make_int4(s, 0, 0, 0);
-    pc[1] = make_int4(0, 0, 0, 0);
+    pcount[k] = s;
 }
 
 // hpre (the LDS binning's per-workgroup prefixes, else null) adds the
@@ -779,7 +781,7 @@ __global__ void k_scatter_points(const float* __restrict__ q, const float* __res
     if (j >= J) return;
     const int c = pcell[j];
     int64_t pos = (int64_t)pstart[c] + prank[j];
-    if (hpre) pos += hpre[(int64_t)((uint32_t)j / (uint32_t)chunk) * NK + c / PSPLIT];  // J < 2^31
+    if (hpre) pos += hpre[(int64_t)((uint32_t)j / (uint32_t)chunk) * NK + c];  // J < 2^31
     ps[pos] = make_float4(q[3 * j], q[3 * j + 1], q[3 * j + 2], aux ? aux[j] : 0.0f);
     if (Oin) pv[pos] = make_float4(Oin[j], lsein[j], 0.0f, 0.0f);
     if (pidx) pidx[pos] = (int)j;
@@ -800,15 +802,20 @@ __global__ void k_scatter_points(const float* __restrict__ q, const float* __res
 // limits scale with W because that per-tile work grows with the window
 // (about W^3 keys) faster than the extra pairs per query (a factor of about
 // (2 + 2 r + 2) / (2 + 2 r), r the cull reach in cells).
-__device__ __forceinline__ int cell_count(const int* __restrict__ pstart, int64_t b, int s)
+// The sorted queries' starts by sort key: sp entries per key (PSPLIT with
+// sub-counters, else 1).
+struct Starts {
+    const int* p;
+    int sp;
+    __device__ __forceinline__ int at(int64_t key) const { return p[key * sp]; }
+};
+
+__device__ __forceinline__ int cell_count(const Starts ps, int64_t b, int s)
 {
-    return pstart[(8 * b + s + 1) * PSPLIT] - pstart[(8 * b + s) * PSPLIT];
+    return ps.at(8 * b + s + 1) - ps.at(8 * b + s);
 }
 
-__device__ __forceinline__ int block_count(const int* __restrict__ pstart, int64_t b)
-{
-    return pstart[8 * (b + 1) * PSPLIT] - pstart[8 * b * PSPLIT];
-}
+__device__ __forceinline__ int block_count(const Starts ps, int64_t b) { return ps.at(8 * (b + 1)) - ps.at(8 * b); }
 
 // With group 2, cells s and s + 1 (s even: adjacent in z) of a block that
 // is split into cell tiles share one tile when both hold queries and
@@ -819,7 +826,7 @@ __device__ __forceinline__ bool cells_merged(int n0, int n1, int cap, int group,
 }
 
 // The z-run of blocks whose queries share block b's tile: (first bz, blocks).
-__device__ __forceinline__ int2 block_run(const int* __restrict__ pstart, int64_t b, int tot, int NB, int cap,
+__device__ __forceinline__ int2 block_run(const Starts ps, int64_t b, int tot, int NB, int cap,
                                           int group, int W)
 {
     const int bz = (int)(b % NB);
@@ -832,7 +839,7 @@ __device__ __forceinline__ int2 block_run(const int* __restrict__ pstart, int64_
         bool all = true;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int n = block_count(pstart, b0 + q0 + i);
+            const int n = block_count(ps, b0 + q0 + i);
             all = all && n > 0;
             sum += n;
         }
@@ -840,57 +847,44 @@ __device__ __forceinline__ int2 block_run(const int* __restrict__ pstart, int64_
     }
     const int p0 = bz & ~1;
     if (p0 + 1 < NB) {
-        const int n0 = block_count(pstart, b0 + p0), n1 = block_count(pstart, b0 + p0 + 1);
+        const int n0 = block_count(ps, b0 + p0), n1 = block_count(ps, b0 + p0 + 1);
         if (n0 > 0 && n1 > 0 && n0 + n1 <= lim2) return make_int2(p0, 2);
     }
     return make_int2(bz, 1);
 }
 
-__global__ void k_block_tiles(int64_t NB3, int NB, const int* __restrict__ pstart, int cap, int group,
-                              const DevStats* __restrict__ st, int* __restrict__ btiles)
+// Tiles of block b; run: the z-run of blocks whose queries share its tile.
+__device__ __forceinline__ int block_tiles(int64_t b, int NB, const Starts ps, int cap, int group, int W, int& tot,
+                                           int2& run)
 {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (b >= NB3) return;
-    const int W = st->W;
-    int tot = 0, split = 0;
+    int split = 0;
+    tot = 0;
 #pragma unroll
     for (int s = 0; s < 8; s += 2) {
-        const int n0 = cell_count(pstart, b, s), n1 = cell_count(pstart, b, s + 1);
+        const int n0 = cell_count(ps, b, s), n1 = cell_count(ps, b, s + 1);
         tot += n0 + n1;
         split += cells_merged(n0, n1, cap, group, W) ? 1 : (n0 + cap - 1) / cap + (n1 + cap - 1) / cap;
     }
-    const int2 run = block_run(pstart, b, tot, NB, cap, group, W);
-    if (run.y > 1) {
-        btiles[b] = (int)(b % NB) == run.x ? 1 : 0;
-        return;
-    }
-    btiles[b] = tot == 0 ? 0 : ((group && tot <= cap) ? 1 : split);
+    run = block_run(ps, b, tot, NB, cap, group, W);
+    if (run.y > 1) return (int)(b % NB) == run.x ? 1 : 0;
+    return tot == 0 ? 0 : ((group && tot <= cap) ? 1 : split);
 }
 
+// Writes block b's tiles (block_tiles() of them) from tiles[t] on.
 // Tile descriptor: (first cell, first query, queries, extents | slice << 5);
 // extents: bit 0 x, bit 1 y (cells - 1, 0..1), bits 2-4 z (cells - 1, 0..7).
-__global__ void k_build_tiles(int64_t NB3, Geo g, const int* __restrict__ pstart, int cap, int group,
-                              const DevStats* __restrict__ st, const int* __restrict__ tstart,
-                              int4* __restrict__ tiles)
+__device__ __forceinline__ void write_tiles(int64_t b, const Geo& g, const Starts ps, int cap, int group, int W, int tot,
+                                            const int2 run, int t, int4* __restrict__ tiles)
 {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (b >= NB3) return;
-    const int nt = tstart[b + 1] - tstart[b];
-    if (nt == 0) return;
     const int NB = g.NB, C1 = g.C1;
     const int bx = (int)(b / ((int64_t)NB * NB)), by = (int)((b / NB) % NB), bz = (int)(b % NB);
-    const int first = pstart[8 * b * PSPLIT];
-    int t = tstart[b];
-    int tot = 0;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) tot += cell_count(pstart, b, s);
+    const int first = ps.at(8 * b);
     const int ex = min(2, C1 - 2 * bx), ey = min(2, C1 - 2 * by);
     const int c0 = ((2 * bx) * C1 + 2 * by) * C1 + 2 * bz;
-    const int2 run = block_run(pstart, b, tot, NB, cap, group, st->W);
     if (run.y > 1) {  // b leads the run (the others have no tiles)
         int n = 0, ez = 0;
         for (int i = 0; i < run.y; ++i) {
-            n += block_count(pstart, b + i);
+            n += block_count(ps, b + i);
             ez += min(2, C1 - 2 * (bz + i));
         }
         tiles[t] = make_int4(c0, first, n, (ex - 1) | ((ey - 1) << 1) | ((ez - 1) << 2));
@@ -902,13 +896,13 @@ __global__ void k_build_tiles(int64_t NB3, Geo g, const int* __restrict__ pstart
         return;
     }
     for (int s = 0; s < 8; ++s) {
-        const int n = cell_count(pstart, b, s);
+        const int n = cell_count(ps, b, s);
         const int cx = 2 * bx + (s >> 2), cy = 2 * by + ((s >> 1) & 1), cz = 2 * bz + (s & 1);
         const int c = (cx * C1 + cy) * C1 + cz;
-        const int start = pstart[(8 * b + s) * PSPLIT];
+        const int start = ps.at(8 * b + s);
         if (!(s & 1)) {
-            const int n1 = cell_count(pstart, b, s + 1);
-            if (cells_merged(n, n1, cap, group, st->W)) {  // cells s and s + 1: z extent 2
+            const int n1 = cell_count(ps, b, s + 1);
+            if (cells_merged(n, n1, cap, group, W)) {  // cells s and s + 1: z extent 2
                 tiles[t++] = make_int4(c, start, n + n1, 1 << 2);
                 ++s;
                 continue;
@@ -924,47 +918,148 @@ __global__ void k_build_tiles(int64_t NB3, Geo g, const int* __restrict__ pstart
     }
 }
 
-// Cost of each tile, one wave per tile (grid-stride over the tiles): its
-// queries times the keys of its window (before the block-level truncation),
-// bucketed on a log2 scale; the lanes sum the moved keys of the window's rows.
-__global__ __launch_bounds__(BLOCK) void k_tile_cost(const int* __restrict__ ntiles, Geo g, int offsets,
-                                                     const int* __restrict__ mstart,
-                                                     const int4* __restrict__ tiles,
-                                                     int2* __restrict__ tbucket, DevStats* __restrict__ st)
+// Tiles of every block in one kernel: each wave takes a range of the tile list
+// with one atomic, so the list's order is the waves' (the queue is ordered by
+// cost below; deterministic mode, whose loss sums follow the list, counts,
+// scans and builds instead).
+__global__ __launch_bounds__(BLOCK) void k_make_tiles(int64_t NB3, Geo g, Starts ps, int cap, int group,
+                                                      const DevStats* __restrict__ st, int* __restrict__ ntiles,
+                                                      int4* __restrict__ tiles)
+{
+    const int64_t b = blockIdx.x * (int64_t)BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & 63, W = st->W;
+    int tot = 0, n = 0;
+    int2 run = make_int2(0, 1);
+    if (b < NB3) n = block_tiles(b, g.NB, ps, cap, group, W, tot, run);
+    int inc = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += u;
+    }
+    int base = 0;
+    if (lane == 63 && inc) base = atomicAdd(ntiles, inc);
+    base = __shfl(base, 63, 64);
+    if (n) write_tiles(b, g, ps, cap, group, W, tot, run, base + inc - n, tiles);
+}
+
+__global__ void k_block_tiles(int64_t NB3, int NB, Starts ps, int cap, int group, const DevStats* __restrict__ st,
+                              int* __restrict__ btiles)
+{
+    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (b >= NB3) return;
+    int tot;
+    int2 run;
+    btiles[b] = block_tiles(b, NB, ps, cap, group, st->W, tot, run);
+}
+
+__global__ void k_build_tiles(int64_t NB3, Geo g, Starts ps, int cap, int group, const DevStats* __restrict__ st,
+                              const int* __restrict__ tstart, int4* __restrict__ tiles)
+{
+    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (b >= NB3 || tstart[b + 1] == tstart[b]) return;
+    int tot;
+    int2 run;
+    block_tiles(b, g.NB, ps, cap, group, st->W, tot, run);
+    write_tiles(b, g, ps, cap, group, st->W, tot, run, tstart[b], tiles);
+}
+
+// Cost bucket of a tile (one wave): its queries times the keys of its window
+// (before the block-level truncation) on a log2 scale; the lanes sum the moved
+// keys of the window's rows.
+__device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offsets, int W, const int* __restrict__ mstart)
 {
     const int lane = threadIdx.x & 63;
-    const int nw = (int)(gridDim.x * (BLOCK / 64));
-    const int n = *ntiles;
-    const int C1 = g.C1, R = g.R, W = st->W;
-    for (int t = (int)((blockIdx.x * (int64_t)BLOCK + threadIdx.x) >> 6); t < n; t += nw) {
-        const int4 tl = tiles[t];
-        const int cx = tl.x / (C1 * C1), cy = (tl.x / C1) % C1, cz = tl.x % C1;
-        const int cx1 = cx + (tl.w & 1), cy1 = cy + ((tl.w >> 1) & 1), cz1 = cz + ((tl.w >> 2) & 7);
-        long long K = 0;
-        if (offsets) {
-            const int mx0 = max(cx - W, 0), mx1 = min(cx1 + W, C1 - 1);
-            const int my0 = max(cy - W, 0), my1 = min(cy1 + W, C1 - 1);
-            const int mz0 = max(cz - W, 0), mz1 = min(cz1 + W, C1 - 1);
-            const int nmy = my1 - my0 + 1, nrow = (mx1 - mx0 + 1) * nmy;
-            for (int r = lane; r < nrow; r += 64) {
-                const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
-                K += mstart[row + mz1 + 1] - mstart[row + mz0];
-            }
-            K = wave_sum(K);
+    const int C1 = g.C1, R = g.R;
+    const int cx = tl.x / (C1 * C1), cy = (tl.x / C1) % C1, cz = tl.x % C1;
+    const int cx1 = cx + (tl.w & 1), cy1 = cy + ((tl.w >> 1) & 1), cz1 = cz + ((tl.w >> 2) & 7);
+    int K = 0;
+    if (offsets) {
+        const int mx0 = max(cx - W, 0), mx1 = min(cx1 + W, C1 - 1);
+        const int my0 = max(cy - W, 0), my1 = min(cy1 + W, C1 - 1);
+        const int mz0 = max(cz - W, 0), mz1 = min(cz1 + W, C1 - 1);
+        const int nmy = my1 - my0 + 1, nrow = (mx1 - mx0 + 1) * nmy;
+        for (int r = lane; r < nrow; r += 64) {
+            const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
+            K += mstart[row + mz1 + 1] - mstart[row + mz0];
         }
-        if (lane == 0) {
-            K += (long long)(min(cx1 + W, R - 1) - max(cx - W + 1, 0) + 1) *
-                 (min(cy1 + W, R - 1) - max(cy - W + 1, 0) + 1) *
-                 (min(cz1 + W, R - 1) - max(cz - W + 1, 0) + 1);
-            const float c = (float)(K * (long long)tl.z);
-            const int bk = min(127, max(0, (int)(4.0f * log2f(fmaxf(c, 1.0f)))));
-            // sort key (descending): cost bucket, then ascending slice index
-            tbucket[t] = make_int2(bk * SLICE_KEYS + (SLICE_KEYS - 1 - (tl.w >> 5)), 0);
+        K = wave_sum(K);
+    }
+    K += (min(cx1 + W, R - 1) - max(cx - W + 1, 0) + 1) * (min(cy1 + W, R - 1) - max(cy - W + 1, 0) + 1) *
+         (min(cz1 + W, R - 1) - max(cz - W + 1, 0) + 1);
+    const float c = (float)K * (float)tl.z;
+    return min(127, max(0, (int)(4.0f * log2f(fmaxf(c, 1.0f)))));
+}
+
+// Each tile's cost bucket and its rank among the bucket's tiles, and the
+// bucket counts.  A workgroup takes up to COST_TILES tiles, one wave each in
+// turn, counts them per bucket in LDS and takes a range of every bucket's
+// ranks with one atomic.  Its tiles lie apart in the list: slices of one dense
+// cell share their whole key window, and queued back to back they would flush
+// to the same gradient records at once.
+constexpr int COST_TILES = 32;
+
+__global__ __launch_bounds__(BLOCK) void k_tile_cost(const int* __restrict__ ntiles, Geo g, int offsets,
+                                                     const int* __restrict__ mstart, const int4* __restrict__ tiles,
+                                                     int2* __restrict__ tbucket, DevStats* __restrict__ st)
+{
+    __shared__ int sb[COST_TILES], hist[128], base[128];
+    const int tid = threadIdx.x, n = *ntiles, W = st->W;
+    const int G = (n + COST_TILES - 1) / COST_TILES;  // tile c + i G is number i of chunk c
+    for (int c = blockIdx.x; c < G; c += gridDim.x) {
+        if (tid < 128) hist[tid] = 0;
+        for (int i = tid >> 6; i < COST_TILES; i += BLOCK / 64) {
+            const int t = c + i * G;
+            const int bk = t < n ? tile_bucket(tiles[t], g, offsets, W, mstart) : 0;
+            if ((tid & 63) == 0) sb[i] = bk;
         }
+        __syncthreads();
+        const int t = c + tid * G;
+        const bool ok = tid < COST_TILES && t < n;
+        int r = 0;
+        if (ok) r = atomicAdd(&hist[sb[tid]], 1);
+        __syncthreads();
+        if (tid < 128 && hist[tid]) base[tid] = atomicAdd(&st->bcount[tid], hist[tid]);
+        __syncthreads();
+        if (ok) tbucket[t] = make_int2(sb[tid], base[sb[tid]] + r);
+        __syncthreads();
     }
 }
 
-// Stable counting sort of the tiles by descending cost bucket, then by
+// tout[position] = tile, in descending bucket order.
+__global__ __launch_bounds__(BLOCK) void k_tile_order(const int* __restrict__ ntiles, const int2* __restrict__ tbucket,
+                                                      const DevStats* __restrict__ st, const int4* __restrict__ tin,
+                                                      int4* __restrict__ tout)
+{
+    __shared__ int first[128], sh[BLOCK / 64];
+    const int n = *ntiles;
+    if (blockIdx.x * BLOCK >= n) return;
+    const int i = threadIdx.x;
+    int tot;
+    const int f = block_excl_scan(i < 128 ? st->bcount[127 - i] : 0, sh, &tot);
+    if (i < 128) first[127 - i] = f;
+    __syncthreads();
+    for (int t = blockIdx.x * BLOCK + i; t < n; t += gridDim.x * BLOCK) {
+        const int2 e = tbucket[t];
+        tout[first[e.x] + e.y] = tin[t];
+    }
+}
+
+// Deterministic mode: the sort keys of k_tile_rank, one wave per tile.
+__global__ __launch_bounds__(BLOCK) void k_tile_keys(const int* __restrict__ ntiles, Geo g, int offsets,
+                                                     const int* __restrict__ mstart, const int4* __restrict__ tiles,
+                                                     int2* __restrict__ tbucket, const DevStats* __restrict__ st)
+{
+    const int nw = (int)(gridDim.x * (BLOCK / 64)), n = *ntiles, W = st->W;
+    for (int t = (int)((blockIdx.x * (int64_t)BLOCK + threadIdx.x) >> 6); t < n; t += nw) {
+        const int4 tl = tiles[t];
+        const int bk = tile_bucket(tl, g, offsets, W, mstart);
+        // sort key (descending): cost bucket, then ascending slice index
+        if ((threadIdx.x & 63) == 0) tbucket[t] = make_int2(bk * SLICE_KEYS + (SLICE_KEYS - 1 - (tl.w >> 5)), 0);
+    }
+}
+
+// Deterministic mode's stable counting sort of the tiles by descending cost bucket, then by
 // ascending slice index (slices of one dense cell share their whole key
 // window, so running them back to back would have concurrent workgroups
 // flush atomics to the same keys), then block-major (spatial) order, so that
@@ -1014,11 +1109,10 @@ __global__ __launch_bounds__(BLOCK) void k_tile_rank(const int* __restrict__ nti
     }
 }
 
-// Pass 2 (after the scan of chist into cstart): final position of every tile
-// in the sorted order; tbucket becomes (cost bucket, rank inside the bucket).
-// tout may be null (the batched path orders all shapes' tiles together).
+// Pass 2 (after the scan of chist into cstart): every tile to its position in
+// the sorted order.
 __global__ __launch_bounds__(BLOCK) void k_tile_place(const int* __restrict__ ntiles,
-                                                      int2* __restrict__ tbucket, int nch,
+                                                      const int2* __restrict__ tbucket, int nch,
                                                       const int* __restrict__ cstart,
                                                       const int4* __restrict__ tin,
                                                       int4* __restrict__ tout)
@@ -1027,12 +1121,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_place(const int* __restrict__ nt
     const int t = blockIdx.x * BLOCK + threadIdx.x;
     if (t >= *ntiles) return;
     const int2 e = tbucket[t];
-    const int bucket = e.x / SLICE_KEYS;
-    const int pos = cstart[(NKEY - 1 - e.x) * nch + blockIdx.x] + e.y;
-    // the bucket's first key row is its largest slice key
-    const int first = cstart[(NKEY - 1 - (bucket * SLICE_KEYS + SLICE_KEYS - 1)) * nch];
-    tbucket[t] = make_int2(bucket, pos - first);
-    if (tout) tout[pos] = tin[t];
+    tout[cstart[(NKEY - 1 - e.x) * nch + blockIdx.x] + e.y] = tin[t];
 }
 
 // ------------------------------------------------------------------ tiles
@@ -2240,6 +2329,7 @@ __device__ __forceinline__ void fallback_run(const TileArgs& a)
     const int64_t ng = L.grid ? I : 0;  // grid keys first, then moved keys
     const int64_t nkeys = ng + (L.moved ? I : 0);
     const int nfb = a.st->nfb;
+    if (a.n_uncertified && blockIdx.x == 0 && tid == 0) *a.n_uncertified = nfb;
     for (;;) {
         __syncthreads();
         if (tid == 0) s_item = atomicAdd(&a.st->fbqueue, 1);
@@ -2428,40 +2518,23 @@ __global__ __launch_bounds__(FB_BLOCK) void k_fallback_batch(const TileArgs* __r
     }
 }
 
-// Moved keys' gradient records (binned order, flush slots) added to grad
-// at their vertices, and cleared.  Every vertex has one moved key, so no two
-// records meet.
-template <int DEG>
-__device__ __forceinline__ void slot_finalize(const TileArgs& a, int64_t p)
+// The keys' gradient records added to grad and cleared, one thread per channel
+// (neighbouring threads on neighbouring channels; a thread per record took 32
+// us at 32^3): a grid channel (c < ngrid) from its vertex's record, a moved one
+// from the record that the binning gave the vertex's moved key.
+__global__ void k_slot_finalize(float* __restrict__ grad, float* __restrict__ gslotg, float* __restrict__ gslot,
+                                const int* __restrict__ mslot, int64_t n, int nch, int ngrid, int nfl)
 {
-    constexpr int MW = mk_width(DEG), NF = flush_slots(DEG);
-    auto add = [&](float* g, float* d, int n) {
-        for (int sl = 0; sl < n; ++sl) {
-            const float x = g[sl];
-            if (x != 0.0f) {
-                d[sl] += x;
-                g[sl] = 0.0f;
-            }
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t vx = (uint32_t)i / (uint32_t)nch;  // n < 2^32
+        const int c = (int)((uint32_t)i - vx * (uint32_t)nch);
+        float* gs = c < ngrid ? gslotg + (int64_t)vx * nfl + c : gslot + (int64_t)mslot[vx] * nfl + (c - ngrid);
+        const float x = *gs;
+        if (x != 0.0f) {
+            grad[i] += x;
+            *gs = 0.0f;
         }
-    };
-    if (a.offsets) {  // moved key of record p: Delta, values, rho'
-        const int64_t v = __float_as_int(a.mk[MW * p + 2].w);
-        add(a.gslot + p * NF, a.grad + v * a.L.nch + a.L.mdel, a.L.nch - a.L.mdel);
     }
-    if (a.L.grid)  // grid key of vertex p: values, rho
-        add(a.gslotg + p * NF, a.grad + p * a.L.nch, a.L.moved ? a.L.mdel : a.L.nch);
-}
-
-template <int DEG>
-__global__ void k_slot_finalize(TileArgs a)
-{
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < a.I; p += (int64_t)gridDim.x * blockDim.x)
-        slot_finalize<DEG>(a, p);
-}
-
-__global__ void k_count_uncertified(const DevStats* st, int64_t* out)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *out = (int64_t)st->nfb;
 }
 
 // ------------------------------------------------------------- loss, Adam
@@ -2469,30 +2542,29 @@ __global__ void k_count_uncertified(const DevStats* st, int64_t* out)
 // per thread (clamped addresses, selected sums) ahead of the additions.
 constexpr int LF_BLOCK = 1024;
 
-__global__ __launch_bounds__(LF_BLOCK) void k_loss_finalize(const double2* __restrict__ lpart,
-                                                            const DevStats* __restrict__ st,
-                                                            const DetStats* __restrict__ det,
-                                                            double invJ, double* __restrict__ out)
+template <int NT>
+__device__ __forceinline__ void loss_finalize(const double2* __restrict__ lpart, const DevStats* __restrict__ st,
+                                              const DetStats* __restrict__ det, double invJ, double* __restrict__ out)
 {
-    __shared__ double sh[LF_BLOCK / 64];
+    __shared__ double sh[NT / 64];
     const int n = st->nitems;
     double s2 = 0.0, s1 = 0.0;
-    for (int t0 = threadIdx.x; t0 < n; t0 += 4 * LF_BLOCK) {
+    for (int t0 = threadIdx.x; t0 < n; t0 += 4 * NT) {
         double2 v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int t = t0 + u * LF_BLOCK;
+            const int t = t0 + u * NT;
             v[u] = lpart[t < n ? t : n - 1];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const bool ok = t0 + u * LF_BLOCK < n;
+            const bool ok = t0 + u * NT < n;
             s2 += ok ? v[u].x : 0.0;
             s1 += ok ? v[u].y : 0.0;
         }
     }
-    s2 = block_sum<double, LF_BLOCK>(s2, sh);
-    s1 = block_sum<double, LF_BLOCK>(s1, sh);
+    s2 = block_sum<double, NT>(s2, sh);
+    s1 = block_sum<double, NT>(s1, sh);
     if (threadIdx.x == 0) {
         // fallback queries' sums: fixed point in deterministic mode
         const double f2 = det ? (double)(long long)det->fbfix[0] / det->lscale[0] : st->fb_loss[0];
@@ -2500,6 +2572,14 @@ __global__ __launch_bounds__(LF_BLOCK) void k_loss_finalize(const double2* __res
         out[0] = (s2 + f2) * invJ;
         out[1] = (s1 + f1) * invJ;
     }
+}
+
+__global__ __launch_bounds__(LF_BLOCK) void k_loss_finalize(const double2* __restrict__ lpart,
+                                                            const DevStats* __restrict__ st,
+                                                            const DetStats* __restrict__ det, double invJ,
+                                                            double* __restrict__ out)
+{
+    loss_finalize<LF_BLOCK>(lpart, st, det, invJ, out);
 }
 
 // AdamW with decoupled weight decay and bias correction; clears the gradient.
@@ -2524,14 +2604,22 @@ __global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* 
 // channel is grad plus its slot in its key's record, for a grid channel
 // (c < ngrid) the vertex's record in gslotg, for a moved one the record the
 // binning gave the vertex's moved key (mslot) in gslot; all are cleared.
-// n = nch I < 2^32.
-__global__ void k_adam_fit(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
+// n = nch I < 2^32.  With out the first workgroup reduces the loss instead (one
+// launch for both).
+__global__ __launch_bounds__(BLOCK) void k_adam_fit(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
                            float* __restrict__ grad, float* __restrict__ gslotg, float* __restrict__ gslot,
                            const int* __restrict__ mslot, int64_t n, int nch, int ngrid, int nfl, float lr,
-                           float b1, float b2, float eps, float wd, float bc1, float bc2)
+                           float b1, float b2, float eps, float wd, float bc1, float bc2,
+                           const double2* __restrict__ lpart, const DevStats* __restrict__ st, double invJ,
+                           double* __restrict__ out)
 {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    const int skip = out ? 1 : 0;
+    if ((int)blockIdx.x < skip) {
+        loss_finalize<BLOCK>(lpart, st, nullptr, invJ, out);
+        return;
+    }
+    for (int64_t i = (blockIdx.x - skip) * (int64_t)BLOCK + threadIdx.x; i < n;
+         i += (int64_t)(gridDim.x - skip) * BLOCK) {
         float gi = grad[i];
         const uint32_t vx = (uint32_t)i / (uint32_t)nch;
         const int c = (int)((uint32_t)i - vx * (uint32_t)nch);
@@ -2738,16 +2826,13 @@ static hipError_t scan(const int* cnt, int64_t n, int* blk, int* start, hipStrea
     return hipGetLastError();
 }
 
-// Stable sort of positions [0, n) by keys (values < nkeys), one 8-bit digit
-// per pass; *out receives the sorted positions (a workspace buffer).
-// Stable sort of n keys in [0, nkeys) whose low `low` bits are zero (those
-// bits take no pass); *out receives the input positions in sorted order.
-static hipError_t radix_sort(const Work& w, const int* keys, int64_t n, int64_t nkeys, int low, const int** out,
-                             hipStream_t s)
+// Stable sort of n keys in [0, nkeys), one 8-bit digit per pass; *out receives
+// the input positions in sorted order (a workspace buffer).
+static hipError_t radix_sort(const Work& w, const int* keys, int64_t n, int64_t nkeys, const int** out, hipStream_t s)
 {
     int bits = 0;
     while (bits < 31 && (1ll << bits) < nkeys) ++bits;
-    const int passes = bits > low ? (bits - low + 7) / 8 : 1;
+    const int passes = bits > 0 ? (bits + 7) / 8 : 1;
     const int64_t nb = (n + RS_TILE - 1) / RS_TILE;
     if (n > w.rs_n) return hipErrorInvalidValue;
     const int* kin = keys;
@@ -2755,10 +2840,10 @@ static hipError_t radix_sort(const Work& w, const int* keys, int64_t n, int64_t 
     for (int pass = 0; pass < passes; ++pass) {
         int* ko = w.rs_k[pass & 1];
         int* vo = w.rs_v[pass & 1];
-        k_rs_hist<<<(unsigned)nb, BLOCK, 0, s>>>(kin, n, low + 8 * pass, (int)nb, w.rs_hist);
+        k_rs_hist<<<(unsigned)nb, BLOCK, 0, s>>>(kin, n, 8 * pass, (int)nb, w.rs_hist);
         hipError_t e = scan(w.rs_hist, 256 * nb, w.rs_blk, w.rs_hist + 256 * w.rs_nb + 1, s);
         if (e != hipSuccess) return e;
-        k_rs_scatter<<<(unsigned)nb, BLOCK, 0, s>>>(kin, vin, n, low + 8 * pass, (int)nb, w.rs_hist + 256 * w.rs_nb + 1,
+        k_rs_scatter<<<(unsigned)nb, BLOCK, 0, s>>>(kin, vin, n, 8 * pass, (int)nb, w.rs_hist + 256 * w.rs_nb + 1,
                                                     ko, vo);
         kin = ko;
         vin = vo;
@@ -2784,13 +2869,13 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
     // Deterministic mode: the query counts (exact totals whatever the order
     // of the atomics) and sort keys come from either binning; both orders come
     // from stable radix sorts, so every float sum runs in an order fixed by
-    // the data.  The LDS binning puts every query of a key in sub-counter 0:
-    // its keys are multiples of PSPLIT, whose low bits the sort skips.
+    // the data.
     const bool det = w.det != nullptr;
     const bool lbin = w.hist != nullptr;
     {
         const int64_t na = p.offsets ? C : 0, nb = lbin ? 0 : w.NK * PSPLIT;
-        k_reset_front<<<grid_for(na > nb ? na : nb, BLOCK * 8), BLOCK, 0, s>>>(w.st, w.mcount, na, w.pcount, nb);
+        k_reset_front<<<grid_for(na > nb ? na : nb, BLOCK * 8), BLOCK, 0, s>>>(w.st, w.tstart + w.NB3, w.mcount, na,
+                                                                               w.pcount, nb);
     }
     if (det) {
         k_det_reset<<<1, 64, 0, s>>>(w.det);
@@ -2824,7 +2909,7 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
         if (e != hipSuccess) return e;
         if (det) {
             const int* sorted = nullptr;
-            e = radix_sort(w, w.mcell, I, C, 0, &sorted, s);
+            e = radix_sort(w, w.mcell, I, C, &sorted, s);
             if (e != hipSuccess) return e;
             if (p.L.degree == 2)
                 k_det_gather_keys<2><<<grid_for(I), BLOCK, 0, s>>>(sorted, I, w.mrec, w.mk);
@@ -2836,7 +2921,6 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
             k_scatter_keys<1><<<grid_for(I), BLOCK, 0, s>>>(I, w.mcell, w.mrank, w.mstart, w.mrec, w.mk, w.mslot);
         }
     }
-    k_window<<<1, 64, 0, s>>>(w.st, g, p.T, p.window);
     // queries
     int64_t nw = (J + LBIN_PER - 1) / LBIN_PER;
     if (nw > w.lnw) nw = w.lnw;
@@ -2844,20 +2928,20 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
     const int64_t chunk = J > 0 ? (J + nw - 1) / nw : 1;
     if (lbin) {
         k_count_points_lds<<<(unsigned)nw, LBIN_BLOCK, 0, s>>>(p.q, J, chunk, g, (int)w.NK, w.pcell, w.prank,
-                                                                w.hist);
+                                                                w.hist, w.st, p.T, p.window);
         k_hist_prefix<<<grid_for(w.NK), BLOCK, 0, s>>>(w.hist, (int)nw, (int)w.NK, w.pcount);
     } else {
-        k_count_points<<<grid_for(J), BLOCK, 0, s>>>(p.q, J, g, w.pcell, w.prank, w.pcount);
+        k_count_points<<<grid_for(J), BLOCK, 0, s>>>(p.q, J, g, w.pcell, w.prank, w.pcount, w.st, p.T, p.window);
     }
+    const Starts ps = {w.pstart, lbin ? 1 : PSPLIT};
     {
-        hipError_t e = scan(w.pcount, w.NK * PSPLIT, w.scan_blk, w.pstart, s);
+        hipError_t e = scan(w.pcount, w.NK * ps.sp, w.scan_blk, w.pstart, s);
         if (e != hipSuccess) return e;
     }
     // the fit step writes no per-query outputs and needs no original indices
     if (det) {
         const int* sorted = nullptr;
-        static_assert(PSPLIT == 8, "three low key bits");
-        hipError_t e = radix_sort(w, w.pcell, J, w.NK * PSPLIT, lbin ? 3 : 0, &sorted, s);
+        hipError_t e = radix_sort(w, w.pcell, J, w.NK * ps.sp, &sorted, s);
         if (e != hipSuccess) return e;
         k_det_gather_points<<<grid_for(J), BLOCK, 0, s>>>(sorted, p.q, p.aux, p.O_in, p.lse_in, J, w.ps, w.pv,
                                                           mode == MODE_FIT ? nullptr : w.pidx);
@@ -2866,24 +2950,26 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
                                                        w.prank, w.pstart, lbin ? w.hist : nullptr, chunk,
                                                        (int)w.NK, w.ps, w.pv, mode == MODE_FIT ? nullptr : w.pidx);
     }
-    k_block_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g.NB, w.pstart, w.cap, w.group, w.st, w.btiles);
-    {
-        hipError_t e = scan(w.btiles, w.NB3, w.scan_blk, w.tstart, s);
-        if (e != hipSuccess) return e;
-    }
-    k_build_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g, w.pstart, w.cap, w.group, w.st, w.tstart,
-                                                    w.tiles_tmp);
-    int64_t cgrid = (w.max_tiles + BLOCK / 64 - 1) / (BLOCK / 64);
+    const int* ntiles = w.tstart + w.NB3;
+    int64_t cgrid = (w.max_tiles + COST_TILES - 1) / COST_TILES;
     if (cgrid > (int64_t)w.num_cu * 16) cgrid = (int64_t)w.num_cu * 16;
-    k_tile_cost<<<(unsigned)cgrid, BLOCK, 0, s>>>(w.tstart + w.NB3, g, p.offsets, w.mstart,
-                                                  w.tiles_tmp, w.tbucket, w.st);
-    k_tile_rank<<<(unsigned)w.nch, BLOCK, 0, s>>>(w.tstart + w.NB3, w.tbucket, (int)w.nch, w.chist, w.st);
-    {
-        hipError_t e = scan(w.chist, 128 * SLICE_KEYS * w.nch, w.scan_blk, w.cstart, s);
-        if (e != hipSuccess) return e;
+    if (!det) {
+        k_make_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g, ps, w.cap, w.group, w.st, w.tstart + w.NB3, w.tiles_tmp);
+        k_tile_cost<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, w.mstart, w.tiles_tmp, w.tbucket, w.st);
+        // the batched path orders all shapes' tiles together
+        if (ordered)
+            k_tile_order<<<grid_for(w.max_tiles), BLOCK, 0, s>>>(ntiles, w.tbucket, w.st, w.tiles_tmp, w.tiles);
+        return hipGetLastError();
     }
-    k_tile_place<<<(unsigned)w.nch, BLOCK, 0, s>>>(w.tstart + w.NB3, w.tbucket, (int)w.nch, w.cstart,
-                                                   w.tiles_tmp, ordered ? w.tiles : nullptr);
+    k_block_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g.NB, ps, w.cap, w.group, w.st, w.btiles);
+    hipError_t e = scan(w.btiles, w.NB3, w.scan_blk, w.tstart, s);
+    if (e != hipSuccess) return e;
+    k_build_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g, ps, w.cap, w.group, w.st, w.tstart, w.tiles_tmp);
+    k_tile_keys<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, w.mstart, w.tiles_tmp, w.tbucket, w.st);
+    k_tile_rank<<<(unsigned)w.nch, BLOCK, 0, s>>>(ntiles, w.tbucket, (int)w.nch, w.chist, w.st);
+    e = scan(w.chist, 128 * SLICE_KEYS * w.nch, w.scan_blk, w.cstart, s);
+    if (e != hipSuccess) return e;
+    k_tile_place<<<(unsigned)w.nch, BLOCK, 0, s>>>(ntiles, w.tbucket, (int)w.nch, w.cstart, w.tiles_tmp, w.tiles);
     return hipGetLastError();
 }
 
@@ -2912,6 +2998,7 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered)
     a.grad = p.grad;
     a.gslot = w.gslot;
     a.gslotg = w.gslotg;
+    a.n_uncertified = p.n_uncertified;
     a.I = w.I;
     a.gfix = w.det ? w.gfix : nullptr;
     a.det = w.det;
@@ -2963,8 +3050,10 @@ hipError_t run_tiles(const Work& w, const Problem& p, Mode mode, hipStream_t s)
     default: launch_tiles<1>(a, mode, p.dOdq_out != nullptr, (unsigned)grid, fgrid, p.ev_stop, s);
     }
     if (mode != MODE_EVAL && !p.defer_slots) {
-        hipError_t e2 = run_slot_finalize(a, s);
-        if (e2 != hipSuccess) return e2;
+        if (!w.det) {
+            hipError_t e2 = run_slot_finalize(w, p.L, p.grad, s);
+            if (e2 != hipSuccess) return e2;
+        }
     }
     if (w.det && mode != MODE_EVAL) {
         const int64_t n = (int64_t)p.L.nch * w.I;
@@ -3034,13 +3123,14 @@ hipError_t run_loss_finalize(const Work& w, int64_t J, double* loss_out, hipStre
 }
 
 hipError_t run_adam_fit(const Work& w, const Layout& L, float* theta, float* m, float* v, float lr,
-                        float beta1, float beta2, float eps, float wd, float bc1, float bc2, hipStream_t s)
+                        float beta1, float beta2, float eps, float wd, float bc1, float bc2, int64_t J,
+                        double* loss_out, hipStream_t s)
 {
     const int64_t n = (int64_t)L.nch * w.I;
     const int ngrid = L.moved ? L.mdel : L.nch;  // grid channels come first
-    k_adam_fit<<<grid_for(n, BLOCK * 4), BLOCK, 0, s>>>(theta, m, v, w.grad, w.gslotg, w.gslot, w.mslot, n, L.nch,
-                                                      ngrid, flush_slots(L.degree), lr, beta1, beta2, eps, wd, bc1,
-                                                      bc2);
+    k_adam_fit<<<grid_for(n, BLOCK * 4) + (loss_out ? 1 : 0), BLOCK, 0, s>>>(
+        theta, m, v, w.grad, w.gslotg, w.gslot, w.mslot, n, L.nch, ngrid, flush_slots(L.degree), lr, beta1, beta2, eps,
+        wd, bc1, bc2, w.lpart, w.st, 1.0 / (double)J, loss_out);
     return hipGetLastError();
 }
 
@@ -3076,20 +3166,11 @@ hipError_t run_lattice(float* t, int R, double lo, double hi, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t run_slot_finalize(const TileArgs& a, hipStream_t s)
+hipError_t run_slot_finalize(const Work& w, const Layout& L, float* grad, hipStream_t s)
 {
-    if (a.gfix) return hipSuccess;
-    const unsigned grid = grid_for(a.I, BLOCK * 4);
-    switch (a.L.degree) {
-    case 2: k_slot_finalize<2><<<grid, BLOCK, 0, s>>>(a); break;
-    default: k_slot_finalize<1><<<grid, BLOCK, 0, s>>>(a);
-    }
-    return hipGetLastError();
-}
-
-hipError_t run_count_uncertified(const Work& w, int64_t* out, hipStream_t s)
-{
-    k_count_uncertified<<<1, 64, 0, s>>>(w.st, out);
+    const int64_t n = (int64_t)L.nch * w.I;
+    k_slot_finalize<<<grid_for(n, BLOCK * 4), BLOCK, 0, s>>>(grad, w.gslotg, w.gslot, w.mslot, n, L.nch,
+                                                            L.moved ? L.mdel : L.nch, flush_slots(L.degree));
     return hipGetLastError();
 }
 
