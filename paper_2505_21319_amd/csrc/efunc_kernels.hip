@@ -1159,7 +1159,7 @@ struct TileSmem {
     float4 pq[PMAX];      // query relative to the tile origin; target, then g = dL/dO (eval: certified)
     float2 pv[PMAX];      // O, lse2 (log2 units); before the forward: 0, reference exponent
     int seg_src[MAXSEG];
-    int seg_off[MAXSEG + 1];
+    int seg_off[MAXSEG];
     float box[BLOCK / 64][8];  // per-wave bounds of the contributing queries
     int isc[2 * (BLOCK / 64)];
     float fsc[BLOCK / 64];
@@ -1355,6 +1355,41 @@ __device__ __forceinline__ void fwd_pair(const TileSmem<DEG>& S, int k, const fl
     m = fmaf(l, f, m);
 }
 
+template <int I>
+__device__ __forceinline__ float quad_bcast(float x)  // lane I of each four
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), I * 0x55, 0xf, 0xf, true));
+}
+
+// The same keys by four lanes (j) in the same order: each lane evaluates every
+// fourth of them, and all four add the four terms up one after the other, 6.5
+// operations per key of the chain instead of 14.
+template <int DEG>
+__device__ __forceinline__ void fwd_quad(const TileSmem<DEG>& S, int n, int ph, int Sf, int j, const float4 q,
+                                         const float M, float& e, float& m)
+{
+#pragma unroll 2
+    for (int k0 = ph; k0 < n; k0 += 4 * Sf) {
+        const int k = k0 + j * Sf, kr = min(k, n - 1);
+        const float4 kc = S.kc[kr], kv = S.kv[kr];
+        const KeyQ<DEG> kq = load_q(S, kr);
+        const float dx = q.x - kc.x, dy = q.y - kc.y, dz = q.z - kc.z;
+        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        float l = ex2(fmaf(kc.w, r2, -M));
+        float f = poly<DEG>(kv, kq, dx, dy, dz);
+        l = k < n ? l : 0.0f;
+        f = k < n ? f : 0.0f;  // adding 0 leaves e and m as they are
+        e += quad_bcast<0>(l);
+        m = fmaf(quad_bcast<0>(l), quad_bcast<0>(f), m);
+        e += quad_bcast<1>(l);
+        m = fmaf(quad_bcast<1>(l), quad_bcast<1>(f), m);
+        e += quad_bcast<2>(l);
+        m = fmaf(quad_bcast<2>(l), quad_bcast<2>(f), m);
+        e += quad_bcast<3>(l);
+        m = fmaf(quad_bcast<3>(l), quad_bcast<3>(f), m);
+    }
+}
+
 template <int DEG>
 __device__ __forceinline__ void fwd_sums(const TileSmem<DEG>& S, int n, int ph, int Sf, const float4 q,
                                          const float M, float& e, float& m)
@@ -1440,8 +1475,9 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 // One tile: window, forward (Alg. 1), loss, backward (Alg. 2) and flush.
 // td is the tile descriptor, tile its index in a.tiles (loss partial slot);
 // W and bmin2 (smallest beta in log2 units) come from the shape's DevStats;
-// whole is the range of queries of the tile that td is (a piece of), lanes the
-// forward's lanes per query of a piece (0: by the number of queries).
+// whole is the range of queries of the tile that td is (a piece of), keys its
+// part of the window's keys (the x-th of every y), lanes the forward's lanes
+// per query of a piece (0: by the number of queries).
 //
 // Keys reach the pair loops in two steps.  The window's candidates are
 // visited in chunks of KC (grid vertices first, then the moved keys row
@@ -1453,8 +1489,8 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 // kept keys whatever fraction of the window survives the cull.
 template <int MODE, bool QGRAD, int DEG>
 __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, const int4 td, const int2 whole,
-                                         const int lanes, const int tile, const int W, const float bmin2, PairCount& pc,
-                                         const bool add_loss)
+                                         const int2 keys, const int lanes, const int tile, const int W,
+                                         const float bmin2, PairCount& pc, const bool add_loss)
 {
     static_assert(KC == BLOCK, "one staged key per thread");
     constexpr int GW = gk_width(DEG), MW = mk_width(DEG);
@@ -1475,12 +1511,12 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     const int vy0 = max(cy - W + 1, 0), vy1 = min(cy1 + W, R - 1);
     const int vz0 = max(cz - W + 1, 0), vz1 = min(cz1 + W, R - 1);
     const int nvy = vy1 - vy0 + 1, nvz = vz1 - vz0 + 1;
-    const int Kg = L.grid ? (vx1 - vx0 + 1) * nvy * nvz : 0;
+    const int Kg = L.grid ? ((vx1 - vx0 + 1) * nvy * nvz + keys.y - 1 - keys.x) / keys.y : 0;
     const int mx0 = max(cx - W, 0), mx1 = min(cx1 + W, C1 - 1);
     const int my0 = max(cy - W, 0), my1 = min(cy1 + W, C1 - 1);
     const int mz0 = max(cz - W, 0), mz1 = min(cz1 + W, C1 - 1);
     const int nmy = my1 - my0 + 1;
-    const int nrow = a.offsets ? (mx1 - mx0 + 1) * nmy : 0;
+    const int nrow = a.offsets ? ((mx1 - mx0 + 1) * nmy + keys.y - 1 - keys.x) / keys.y : 0;
     const int ngroups = (nrow + MAXSEG - 1) / MAXSEG;
     // Tile origin.  A float32 subtraction rounds the exact difference of
     // two float32 coordinates once, so grid keys and queries are taken
@@ -1515,7 +1551,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         const int r0 = gi * MAXSEG, nr = min(MAXSEG, nrow - r0);
         int len = 0;
         if (tid < nr) {
-            const int r = r0 + tid;
+            const int r = keys.x + (r0 + tid) * keys.y;
             const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
             const int src = a.mstart[row + mz0];
             len = a.mstart[row + mz1 + 1] - src;
@@ -1523,7 +1559,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         }
         int total;
         const int ex = block_excl_scan(len, S.isc, &total);
-        if (tid < nr) S.seg_off[tid] = ex;
+        S.seg_off[tid] = tid < nr ? ex : INT32_MAX;
         grp = gi;
         grpK = __builtin_amdgcn_readfirstlane(total);
         grpN = nr;
@@ -1548,10 +1584,11 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             float4 kc;
             float slack = 0.0f;
             if (grid) {
-                int qx = (int)((float)kk * rdyz);
-                int rr = kk - qx * dyz;
+                const int kg = keys.x + kk * keys.y;
+                int qx = (int)((float)kg * rdyz);
+                int rr = kg - qx * dyz;
                 qx += rr < 0 ? -1 : (rr >= dyz ? 1 : 0);
-                rr = kk - qx * dyz;
+                rr = kg - qx * dyz;
                 int qy = (int)((float)rr * rnz);
                 int rz = rr - qy * nvz;
                 qy += rz < 0 ? -1 : (rz >= nvz ? 1 : 0);
@@ -1562,11 +1599,12 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 kc = make_float4(g.tlat[ix] - oxf, g.tlat[iy] - oyf, g.tlat[iz] - ozf, nb);
                 tag[i] = ix | (iy << 9) | (iz << 18);
             } else {
-                int lo = 0, hi = grpN - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (S.seg_off[mid] <= kk) lo = mid; else hi = mid - 1;
-                }
+                // the last row that starts at or before kk, three probes at a
+                // time (rows past the group's start past every candidate)
+                int lo = 0;
+                for (int st = grpN > 64 ? 64 : 16; st > 0; st >>= 2)
+                    lo += st * ((S.seg_off[lo + st] <= kk ? 1 : 0) + (S.seg_off[lo + 2 * st] <= kk ? 1 : 0) +
+                                (S.seg_off[lo + 3 * st] <= kk ? 1 : 0));
                 const int slot = S.seg_src[lo] + (kk - S.seg_off[lo]);
                 const float4 b0 = a.mk[MW * (int64_t)slot], b2 = a.mk[MW * (int64_t)slot + 2];
                 // float32 centre: within three roundoffs of the loaded one
@@ -1627,8 +1665,9 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             }
         }
     };
-    // The key of tag t in full, centre relative to the tile origin.
-    auto load_key = [&](int t, float4& kc, float4& kv, float4& q0, float2& q1) {
+    // The key of tag t in full, centre relative to the tile origin; t becomes
+    // what the flush addresses it by.
+    auto load_key = [&](int& t, float4& kc, float4& kv, float4& q0, float2& q1) {
         if (t >= 0) {
             const int ix = t & 511, iy = (t >> 9) & 511, iz = t >> 18;
             const int vid = (ix * R + iy) * R + iz;
@@ -1652,6 +1691,8 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                              (float)(((double)b0.y - oy) + (double)b2.y),
                              (float)(((double)b0.z - oz) + (double)b2.z), b0.w);
             kv = b1;
+            // deterministic mode adds the key's gradient up by vertex
+            if (a.gfix) t = -__float_as_int(b2.w) - 1;
         }
     };
     auto put_key = [&](int i, int t, const float4 kc, const float4 kv, const float4 q0, const float2 q1) {
@@ -1667,7 +1708,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     // [0, n); returns the number of moved keys among them.
     auto load_batch = [&](int b, int n) -> int {
         __syncthreads();  // tags complete; the previous batch is no longer read
-        const int t0 = tid < n ? S.cand[b + tid] : 0;
+        int t0 = tid < n ? S.cand[b + tid] : 0;
         if (tid < n) {
             float4 kc, kv, q0;
             float2 q1;
@@ -1679,7 +1720,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     // The same for those of the n tags whose keys reach the box, compacted;
     // returns their number.
     auto load_kept = [&](int b, int n, const float (&bl)[7], float cutoff, int& nmoved) -> int {
-        const int t0 = tid < n ? S.cand[b + tid] : 0;
+        int t0 = tid < n ? S.cand[b + tid] : 0;
         float4 kc, kv, q0;
         float2 q1;
         bool keep = false;
@@ -1717,7 +1758,8 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         Kmt = grpK;
         if (ngroups > 1) {
             int part = 0;
-            for (int r = MAXSEG + tid; r < nrow; r += BLOCK) {
+            for (int i = MAXSEG + tid; i < nrow; i += BLOCK) {
+                const int r = keys.x + i * keys.y;
                 const int row = ((mx0 + r / nmy) * C1 + (my0 + r % nmy)) * C1;
                 part += a.mstart[row + mz1 + 1] - a.mstart[row + mz0];
             }
@@ -1758,7 +1800,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             // exp2(s - M0) <= 2^-M0 per key; keep the sum of K such terms finite
             if (!(-M0 + log2f((float)Kg + (float)Kmt + 1.0f) < 120.0f)) need_exact = 1;
             if (own) S.pv[p] = make_float2(0.0f, M0);
-            if (!own && lanes) continue;
+            if (!own && lanes == 1) continue;
             bl[0] = fminf(bl[0], x); bl[1] = fminf(bl[1], y); bl[2] = fminf(bl[2], z);
             bl[3] = fmaxf(bl[3], x); bl[4] = fmaxf(bl[4], y); bl[5] = fmaxf(bl[5], z);
             bl[6] = fminf(bl[6], M0);
@@ -1774,7 +1816,10 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         const int P1 = min(P, BLOCK), P2 = P - P1;
         const int Sf = lanes ? lanes : max(1, BLOCK / P1);
         const int Sf2 = P2 > 0 ? max(1, BLOCK / P2) : 1;
-        const int pme = tid / Sf, ph = tid - pme * Sf;
+        // a small piece has four lanes for each lane of the whole tile
+        const bool quad = MODE == MODE_FIT && lanes > 0 && P * lanes <= BLOCK / 4;
+        const int lane = quad ? tid >> 2 : tid;
+        const int pme = lane / Sf, ph = lane - pme * Sf;
         const int pme2 = tid / Sf2, ph2 = tid - pme2 * Sf2;
         const bool act = pme < P1;
         const bool act2 = pme2 < P2;
@@ -1799,7 +1844,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             }
             lbase = lend = 0;
             logged = true;
-            S.red[tid].x = M;
+            S.red[lane].x = M;
             S.red[BLOCK + tid].x = M2;
             __syncthreads();
             float mn = INFINITY;
@@ -1829,13 +1874,14 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 fwd_pairs += (unsigned)(n * P);
                 fwd_moved += (unsigned)(nm * P);
                 pc.kept += n;
-                if (act) fwd_sums<DEG>(S, n, ph, Sf, q, Mr, e, m);
+                if (act && quad) fwd_quad<DEG>(S, n, ph, Sf, tid & 3, q, Mr, e, m);
+                else if (act) fwd_sums<DEG>(S, n, ph, Sf, q, Mr, e, m);
                 if (act2) fwd_sums<DEG>(S, n, ph2, Sf2, q2, Mr2, e2, m2);
             }
             pc.cand += ncull;
         }
         __syncthreads();
-        S.red[tid] = make_float2(e, m);
+        S.red[lane] = make_float2(e, m);  // quad: the same from four lanes
         S.red[BLOCK + tid] = make_float2(e2, m2);
         __syncthreads();
 
@@ -1963,8 +2009,10 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             D = fmaxf(D * (1.0f - 1e-5f) - 1e-6f * g.h, 0.0f);
             const bool cert = bmin2 * D * D >= a.T2 - S.pv[p].y;
             if (!cert) {
-                const int slot = atomicAdd(&a.st->nfb, 1);
-                a.fb[slot] = p0 + p;
+                if (keys.x == 0) {  // listed once
+                    const int slot = atomicAdd(&a.st->nfb, 1);
+                    a.fb[slot] = p0 + p;
+                }
                 S.pq[p].w = 0.0f;
             }
         }
@@ -1993,6 +2041,12 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         const int sl = tid % NF;
         const int cg = sl < NV ? L.gval + sl : (sl == NV ? L.grho : -1);
         const int cm = sl < 3 ? L.mdel + sl : (sl < 3 + NV ? L.mval + (sl - 3) : (sl == 3 + NV ? L.mrho : -1));
+
+        double dg = 0.0, dm = 0.0;
+        if (a.gfix) {
+            dg = a.det->dscale[max(cg, 0)];
+            dm = a.det->dscale[max(cm, 0)];
+        }
 
         // The forward's keys that reach these queries: from the forward's
         // tags if S.cand still holds them all (the backward's cut is the
@@ -2099,10 +2153,8 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 const float x = S.fv[sl * FS + kf];
                 if (x == 0.0f) continue;
                 const int64_t rec = mv ? -tg - 1 : ((tg & 511) * R + ((tg >> 9) & 511)) * R + (tg >> 18);
-                if (a.gfix) {
-                    // fixed point by vertex (the moved record carries its vertex)
-                    const int64_t v = mv ? (int64_t)__float_as_int(a.mk[MW * rec + 2].w) : rec;
-                    atomicAdd(a.gfix + v * L.nch + c, fixq(x, a.det->dscale[c]));
+                if (a.gfix) {  // fixed point, by vertex
+                    atomicAdd(a.gfix + rec * L.nch + c, fixq(x, mv ? dm : dg));
                 } else {
                     // consecutive kept moved keys are consecutive records: their
                     // slots share cache lines; a grid key has its vertex's record
@@ -2129,7 +2181,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
 // a few million queries.  Tile kernel at 32^3, whole tiles and cut: fit of 2^21
 // points 1664 and 1056 us, normals at 300,007 points 825 and 370 us, eval of
 // 128^3 lattice points 727 and 436 us; 32,768 points forward and backward 194
-// and 138 us each; shares of 0.25 to 1.0 of a slot's measured within 6 %, 0.12
+// and 118 us each; shares of 0.25 to 1.0 of a slot's measured within 6 %, 0.12
 // 30 % slower.
 struct Items {
     int first[129];   // by descending bucket: first item; [128] their number
@@ -2173,18 +2225,31 @@ __device__ __forceinline__ int find_item(const Items& I, int q, int& piece, int&
     return I.tfirst[lo] + r - piece * cnt;
 }
 
-// Piece j of at most k of tile td: its queries in td.y, td.z (none: false).
-// A fit keeps each query's lanes in the forward (lanes; 0: by the number of
-// queries) as in the whole tile, so that cutting a tile does not change the
-// order in which a query's terms are added: the tile's first 256 queries and
-// the rest are cut apart, and each only if its queries have one lane.
+// Piece j of at most k of tile td: its queries in td.y, td.z, its part of the
+// window's keys (none: false).  A gradient's pieces take all queries and every
+// k-th key: each gathers, loads and flushes only its own keys, so that a tile
+// of few queries and thousands of keys is cut as well (32,768 points backward at
+// 32^3: 160 us cut by queries, 119 by keys).  The others take part of the
+// queries.  A fit adds a query's terms in the same order as in the whole tile:
+// lanes is the number of lanes that share a query there (0: by the number of
+// queries), the tile's first 256 queries and the rest, which have other lanes,
+// are cut apart, and a piece of at most 64 such lanes gives each of them four
+// (fwd_quad).  With one lane each and only tiles of more than 128 queries cut,
+// the forward's chain was half of the longest items: tile kernel of the
+// deterministic fit of 250,007 points at 27^3 382 and 312 us, of 131,072 points of
+// degree 2 at 20^3 229 and 211 us.
 template <int MODE>
-__device__ __forceinline__ bool take_piece(int4& td, int j, int k, int& lanes)
+__device__ __forceinline__ bool take_piece(int4& td, int j, int k, int2& keys, int& lanes)
 {
     lanes = 0;
+    keys = make_int2(0, 1);
     const int P = td.z;
-    constexpr int LEAST = MODE == MODE_FIT ? 64 : 32;  // queries per piece
-    if (MODE != MODE_FIT) {
+    if (MODE == MODE_GRAD) {
+        keys = make_int2(j, k);
+        return true;
+    }
+    constexpr int LEAST = 16;  // queries per piece
+    if (MODE == MODE_EVAL) {
         k = max(1, min(k, (P + LEAST - 1) / LEAST));
         if (j >= k) return false;
         const int lo = j * P / k, hi = (j + 1) * P / k;
@@ -2192,23 +2257,40 @@ __device__ __forceinline__ bool take_piece(int4& td, int j, int k, int& lanes)
         td.z = hi - lo;
         return true;
     }
-    if (k == 1 || P <= BLOCK / 2) return j == 0;
+    if (k == 1) return j == 0;
+    // s1, s2: lanes per query of the two parts; pieces of at least 64 lanes
     const int m1 = min(P, BLOCK), m2 = P - m1;
-    const int k2 = m2 > BLOCK / 2 ? max(1, min(k * m2 / P, (m2 + LEAST - 1) / LEAST)) : (m2 > 0 ? 1 : 0);
-    const int k1 = max(1, min(k - k2, (m1 + LEAST - 1) / LEAST));
+    const int s1 = BLOCK / m1, s2 = m2 > 0 ? BLOCK / m2 : 1;
+    const int n1 = min((s1 * m1 + 63) / 64, (m1 + LEAST - 1) / LEAST);
+    const int n2 = min((s2 * m2 + 63) / 64, (m2 + LEAST - 1) / LEAST);
+    const int k2 = m2 > 0 ? max(1, min(k - n1, n2)) : 0;
+    const int k1 = min(k - k2, n1);
     if (j >= k1 + k2) return false;
     if (j < k1) {
         const int lo = j * m1 / k1, hi = (j + 1) * m1 / k1;
         td.y += lo;
         td.z = hi - lo;
-        lanes = 1;
+        lanes = s1;
     } else {
         const int i = j - k1, lo = i * m2 / k2, hi = (i + 1) * m2 / k2;
         td.y += m1 + lo;
         td.z = hi - lo;
-        lanes = m2 > BLOCK / 2 ? 1 : 0;
+        lanes = s2;
     }
     return true;
+}
+
+// The heaviest items are started first and some of them still end last: their
+// waves go before those of the lighter items on the same SIMD (the heaviest
+// quarter of a full machine's items first).  Tile kernel, without and with:
+// normals of 300,007 points at 32^3 363 and 354 us, deterministic fit of 250,007
+// points at 27^3 342 and 335 us, others within 1 %.
+__device__ __forceinline__ void item_priority(int item, int slots)
+{
+    if (4 * item < slots) __builtin_amdgcn_s_setprio(3);
+    else if (2 * item < slots) __builtin_amdgcn_s_setprio(2);
+    else if (item < slots) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
 }
 
 __device__ __forceinline__ int4 uniform(const int4 v)
@@ -2237,15 +2319,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(S.tile);
         if (item >= nitems) break;
+        item_priority(item, a.slots);
         int j, k, lanes;
+        int2 keys;
         const int t = __builtin_amdgcn_readfirstlane(find_item(I, item, j, k));
         j = __builtin_amdgcn_readfirstlane(j);
         k = __builtin_amdgcn_readfirstlane(k);
         int4 td = uniform(a.tiles[t]);
         const int2 whole = make_int2(td.y, td.z);
-        if (take_piece<MODE>(td, j, k, lanes))
-            tile_run<MODE, QGRAD, DEG>(a, S, td, MODE == MODE_FIT ? whole : make_int2(td.y, td.z), lanes, item, W, bmin2,
-                                       pc, false);
+        if (take_piece<MODE>(td, j, k, keys, lanes))
+            tile_run<MODE, QGRAD, DEG>(a, S, td, MODE == MODE_FIT ? whole : make_int2(td.y, td.z),
+                                       MODE == MODE_GRAD ? keys : make_int2(0, 1), lanes, item, W, bmin2, pc, false);
         else if (MODE == MODE_FIT && threadIdx.x == 0)
             a.lpart[item] = make_double2(0.0, 0.0);
     }
@@ -2287,7 +2371,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
         __syncthreads();
         const int t = __builtin_amdgcn_readfirstlane(S.tile);
         if (t >= n) break;
+        item_priority(t, slots);
         int j, k, lanes;
+        int2 keys;
         const int2 e = gtiles[find_item(I, t, j, k)];
         const int sh = __builtin_amdgcn_readfirstlane(e.x);
         const int lt = __builtin_amdgcn_readfirstlane(e.y);
@@ -2299,9 +2385,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
         const TileArgs a = uniform_args(tab + sh);
         int4 td = uniform(a.tiles[lt]);
         const int2 whole = make_int2(td.y, td.z);
-        if (!take_piece<MODE_FIT>(td, __builtin_amdgcn_readfirstlane(j), __builtin_amdgcn_readfirstlane(k), lanes))
+        if (!take_piece<MODE_FIT>(td, __builtin_amdgcn_readfirstlane(j), __builtin_amdgcn_readfirstlane(k), keys,
+                                  lanes))
             continue;
-        tile_run<MODE_FIT, false, DEG>(a, S, td, whole, lanes, lt, __builtin_amdgcn_readfirstlane(a.st->W),
+        tile_run<MODE_FIT, false, DEG>(a, S, td, whole, make_int2(0, 1), lanes, lt, __builtin_amdgcn_readfirstlane(a.st->W),
                                        __uint_as_float(a.st->bmin_bits) * LOG2E, pc, true);
     }
     if (cur >= 0) flush_pairs(tab[cur].st, pc);
