@@ -45,7 +45,8 @@ struct DevStats {
     int nitems;               // work items of the tile kernel
     int pad0[27];
     int queue;                // tile work-queue head
-    int pad1[31];
+    int bqueue;               // that of the backward of a deterministic fit's cut tiles
+    int pad1[30];
     int nfb;                  // queries appended to the fallback list
     int fbqueue;              // fallback work-queue head
     int pad2[30];
@@ -209,7 +210,7 @@ struct TileArgs {
     const float4* mk;
     const int* mstart;
     const float4* ps;
-    const float4* pv;
+    float4* pv;
     const int* pidx;
     const int4* tiles;
     int slots;          // workgroups that run at a time
@@ -227,6 +228,9 @@ struct TileArgs {
     // deterministic mode (else null): fixed-point gradient and loss sums
     unsigned long long* gfix;
     DetStats* det;
+    // k_tile<GRAD>: the backward of the tiles that a deterministic fit has cut,
+    // pv holding their queries' O, lse (log2 units) and dL/dO
+    int rest, pad;
 };
 
 // Per-shape arguments of the batched tile ordering, loss reduction and AdamW.

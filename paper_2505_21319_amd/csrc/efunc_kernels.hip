@@ -131,6 +131,7 @@ __global__ void k_reset_front(DevStats* st, int* __restrict__ ntiles, int* __res
         st->bgmax_bits = 0u;
         st->W = 1;
         st->queue = 0;
+        st->bqueue = 0;
         st->nfb = 0;
         st->fbqueue = 0;
         st->nonfinite = 0;
@@ -1534,7 +1535,12 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
         S.pq[p] = make_float4(v.x - oxf, v.y - oyf, v.z - ozf, v.w);
         if (MODE == MODE_GRAD) {
             const float4 u = a.pv[p0 + p];
-            S.pv[p] = make_float2(u.x, u.y * LOG2E);
+            if (a.rest) {
+                S.pq[p].w = u.z;
+                S.pv[p] = make_float2(u.x, u.y);
+            } else {
+                S.pv[p] = make_float2(u.x, u.y * LOG2E);
+            }
         }
     }
 
@@ -1768,6 +1774,12 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     }
 
     unsigned long long fwd_pairs = 0ull, fwd_moved = 0ull;
+    // Deterministic mode: a key's gradient is rounded to fixed point once per
+    // tile, and pieces by queries would round it once each (65,028 points at 85^3:
+    // the first moments' error against 64 bits 3.6e-5 instead of 3.3e-5), so the
+    // backward of a cut tile runs in a launch of its own (a.rest), cut by keys:
+    // 250,007 points at 27^3, tile kernels 364 us, 312 with both in one launch.
+    const bool later = MODE == MODE_FIT && lanes > 0 && a.gfix;
 
     if (MODE != MODE_GRAD) {
         __syncthreads();
@@ -1931,7 +1943,9 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                 S.pq[p].w = cert ? 1.0f : 0.0f;
             }
             // an uncertified query's pairs weigh 0 in the backward
-            S.pv[p] = MODE != MODE_FIT || cert ? make_float2(O, lse2) : make_float2(0.0f, INFINITY);
+            const float2 v = MODE != MODE_FIT || cert ? make_float2(O, lse2) : make_float2(0.0f, INFINITY);
+            S.pv[p] = v;
+            if (later) a.pv[p0 + p] = make_float4(v.x, v.y, S.pq[p].w, 0.0f);
         }
         if (MODE == MODE_FIT) {
             lsq = block_sum(lsq, S.dsc);
@@ -2008,7 +2022,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
                             fminf(fminf(pq.y - fly, fhy - pq.y), fminf(pq.z - flz, fhz - pq.z)));
             D = fmaxf(D * (1.0f - 1e-5f) - 1e-6f * g.h, 0.0f);
             const bool cert = bmin2 * D * D >= a.T2 - S.pv[p].y;
-            if (!cert) {
+            if (!cert && !a.rest) {
                 if (keys.x == 0) {  // listed once
                     const int slot = atomicAdd(&a.st->nfb, 1);
                     a.fb[slot] = p0 + p;
@@ -2019,7 +2033,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     }
 
     unsigned long long bwd_pairs = 0ull, bwd_moved = 0ull;
-    if (MODE != MODE_EVAL) {
+    if (MODE != MODE_EVAL && !later) {
         // ---- backward, key-parallel over the tile's queries (Alg. 2)
         // Box and smallest lse2 of the queries that carry a gradient; keys
         // whose every pair with them weighs below e^-T are skipped.
@@ -2189,8 +2203,10 @@ struct Items {
     int pieces[128];  // pieces per tile
 };
 
-// From the tiles per bucket, for a launch whose workgroups fill slots slots.
-__device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bcount, int slots, float* fsh, int* ish)
+// From the tiles per bucket, for a launch whose workgroups fill slots slots;
+// cut: the items of the cut tiles only.
+__device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bcount, int slots, bool cut, float* fsh,
+                                           int* ish)
 {
     const int i = threadIdx.x;
     const int cnt = i < 128 ? bcount[127 - i] : 0;
@@ -2200,7 +2216,7 @@ __device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bco
     const int k = cost > share ? (int)fminf(ceilf(cost / share), (float)MAX_PIECES) : 1;
     int tot;
     const int t0 = block_excl_scan(cnt, ish, &tot);
-    const int f0 = block_excl_scan(i < 128 ? cnt * k : 0, ish, &tot);
+    const int f0 = block_excl_scan(i < 128 && (k > 1 || !cut) ? cnt * k : 0, ish, &tot);
     if (i < 128) {
         I.first[i] = f0;
         I.tfirst[i] = t0;
@@ -2235,9 +2251,8 @@ __device__ __forceinline__ int find_item(const Items& I, int q, int& piece, int&
 // queries), the tile's first 256 queries and the rest, which have other lanes,
 // are cut apart, and a piece of at most 64 such lanes gives each of them four
 // (fwd_quad).  With one lane each and only tiles of more than 128 queries cut,
-// the forward's chain was half of the longest items: tile kernel of the
-// deterministic fit of 250,007 points at 27^3 382 and 312 us, of 131,072 points of
-// degree 2 at 20^3 229 and 211 us.
+// the forward's chain was half of the longest items: tile kernel of a fit of
+// 131,072 points of degree 2 at 20^3 229 and 211 us.
 template <int MODE>
 __device__ __forceinline__ bool take_piece(int4& td, int j, int k, int2& keys, int& lanes)
 {
@@ -2283,8 +2298,8 @@ __device__ __forceinline__ bool take_piece(int4& td, int j, int k, int2& keys, i
 // The heaviest items are started first and some of them still end last: their
 // waves go before those of the lighter items on the same SIMD (the heaviest
 // quarter of a full machine's items first).  Tile kernel, without and with:
-// normals of 300,007 points at 32^3 363 and 354 us, deterministic fit of 250,007
-// points at 27^3 342 and 335 us, others within 1 %.
+// normals of 300,007 points at 32^3 363 and 354 us, a fit of 250,007 points at
+// 27^3 342 and 335 us, others within 1 %.
 __device__ __forceinline__ void item_priority(int item, int slots)
 {
     if (4 * item < slots) __builtin_amdgcn_s_setprio(3);
@@ -2309,13 +2324,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
     __shared__ Items I;
     const int W = __builtin_amdgcn_readfirstlane(a.st->W);
     const float bmin2 = __uint_as_float(a.st->bmin_bits) * LOG2E;
-    plan_items(I, a.st->bcount, a.slots, S.fsc, S.isc);
+    const bool rest = MODE == MODE_GRAD && a.rest;
+    plan_items(I, a.st->bcount, a.slots, rest, S.fsc, S.isc);
     const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
+    if (!rest && blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
     PairCount pc;
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) S.tile = atomicAdd(&a.st->queue, 1);
+        if (threadIdx.x == 0) S.tile = atomicAdd(rest ? &a.st->bqueue : &a.st->queue, 1);
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(S.tile);
         if (item >= nitems) break;
@@ -2361,7 +2377,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
 {
     __shared__ TileSmem<DEG> S;
     __shared__ Items I;
-    plan_items(I, gcount, slots, S.fsc, S.isc);
+    plan_items(I, gcount, slots, false, S.fsc, S.isc);
     const int n = __builtin_amdgcn_readfirstlane(I.first[128]);
     PairCount pc;
     int cur = -1;  // shape whose pair counts pc holds
@@ -3152,6 +3168,7 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered)
     a.I = w.I;
     a.gfix = w.det ? w.gfix : nullptr;
     a.det = w.det;
+    a.rest = 0;
     return a;
 }
 
@@ -3162,6 +3179,11 @@ static void launch_tiles(const TileArgs& a, Mode mode, bool qgrad, unsigned grid
     switch (mode) {
     case MODE_FIT:
         k_tile<MODE_FIT, false, DEG><<<grid, BLOCK, 0, s>>>(a);
+        if (a.gfix) {
+            TileArgs b = a;
+            b.rest = 1;
+            k_tile<MODE_GRAD, false, DEG><<<grid, BLOCK, 0, s>>>(b);
+        }
         if (ev_stop) (void)hipEventRecord(ev_stop, s);
         k_fallback<MODE_FIT, false, DEG><<<fgrid, FB_BLOCK, 0, s>>>(a);
         break;
