@@ -23,10 +23,21 @@ constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
 // Heavy tiles are cut so that no item of the tile kernel's queue is estimated
 // (window keys x queries) above PIECE_SHARE of a workgroup slot's fair share of
 // the work, nor cut below PIECE_LEAST (about 20 us of one workgroup; smaller
-// items pay more for gathering their keys again than the balance gives).
-constexpr int MAX_PIECES = 8;
-constexpr float PIECE_SHARE = 0.75f;
-constexpr float PIECE_LEAST = 1e5f;
+// items pay more for gathering their keys again than the balance gives).  A fit
+// gathers and flushes twice: with its floor at 1e5, 1.4e5 and 1.7e5 a pass over
+// 239,386 points at 6^3 took 193, 172 and 172 us, over 65,536 at 8^3 136, 137 and
+// 140.  A deterministic fit runs the backward of its cut tiles in a launch of its
+// own: shares of 0.75, 1.5 and 2 with floors of 4e5, 2.5e5 and 2.5e5 gave 870, 856
+// and 948 us over 524,288 points at 32^3, 14.3, 13.7 and 13.9 ms over 1,504,109 at 83^3.
+// Its backward's pieces, by keys, are up to MAX_KEY_PIECES per tile: a few tiles of
+// thousands of keys each are all that launch may have (16.4 ms with 8).
+// In a gradient call a key's gather, load and flush count as GRAD_PERKEY queries:
+// 2,093 points forward and backward at 56^3, most tiles one query and up to 28,000
+// keys, 779 us without and 577 with it.
+constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
+constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f;
+constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
+constexpr int GRAD_PERKEY = 32;
 constexpr int SLICE_KEYS = 8;   // slice-index sort keys per cost bucket in the tile order
 constexpr int RS_TILE = 4 * BLOCK;  // elements per workgroup of the deterministic radix sort
 constexpr float LOG2E = 1.4426950408889634f;

@@ -966,9 +966,10 @@ __global__ void k_build_tiles(int64_t NB3, Geo g, Starts ps, int cap, int group,
 }
 
 // Cost bucket of a tile (one wave): its queries times the keys of its window
-// (before the block-level truncation) on a log2 scale; the lanes sum the moved
-// keys of the window's rows.
-__device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offsets, int W, const int* __restrict__ mstart)
+// (before the block-level truncation) on a log2 scale, perkey counting as that
+// many queries more; the lanes sum the moved keys of the window's rows.
+__device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offsets, int W, int perkey,
+                                           const int* __restrict__ mstart)
 {
     const int lane = threadIdx.x & 63;
     const int C1 = g.C1, R = g.R;
@@ -988,7 +989,7 @@ __device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offs
     }
     K += (min(cx1 + W, R - 1) - max(cx - W + 1, 0) + 1) * (min(cy1 + W, R - 1) - max(cy - W + 1, 0) + 1) *
          (min(cz1 + W, R - 1) - max(cz - W + 1, 0) + 1);
-    const float c = (float)K * (float)tl.z;
+    const float c = (float)K * (float)(tl.z + perkey);
     return min(127, max(0, (int)(4.0f * log2f(fmaxf(c, 1.0f)))));
 }
 
@@ -1000,23 +1001,26 @@ __device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offs
 // to the same gradient records at once.
 constexpr int COST_TILES = 32;
 
-__global__ __launch_bounds__(BLOCK) void k_tile_cost(const int* __restrict__ ntiles, Geo g, int offsets,
+__global__ __launch_bounds__(BLOCK) void k_tile_cost(const int* __restrict__ ntiles, Geo g, int offsets, int perkey,
                                                      const int* __restrict__ mstart, const int4* __restrict__ tiles,
                                                      int2* __restrict__ tbucket, DevStats* __restrict__ st)
 {
     __shared__ int sb[COST_TILES], hist[128], base[128];
     const int tid = threadIdx.x, n = *ntiles, W = st->W;
-    const int G = (n + COST_TILES - 1) / COST_TILES;  // tile c + i G is number i of chunk c
+    // few tiles: one per wave and chunk, as the rows of a wide window take a
+    // wave some us (2,093 points at 56^3: 16.7 us with 32 tiles per chunk, now 5)
+    const int ct = min(COST_TILES, max(BLOCK / 64, (n + 4095) / 4096 * (BLOCK / 64)));
+    const int G = (n + ct - 1) / ct;  // tile c + i G is number i of chunk c
     for (int c = blockIdx.x; c < G; c += gridDim.x) {
         if (tid < 128) hist[tid] = 0;
-        for (int i = tid >> 6; i < COST_TILES; i += BLOCK / 64) {
+        for (int i = tid >> 6; i < ct; i += BLOCK / 64) {
             const int t = c + i * G;
-            const int bk = t < n ? tile_bucket(tiles[t], g, offsets, W, mstart) : 0;
+            const int bk = t < n ? tile_bucket(tiles[t], g, offsets, W, perkey, mstart) : 0;
             if ((tid & 63) == 0) sb[i] = bk;
         }
         __syncthreads();
         const int t = c + tid * G;
-        const bool ok = tid < COST_TILES && t < n;
+        const bool ok = tid < ct && t < n;
         int r = 0;
         if (ok) r = atomicAdd(&hist[sb[tid]], 1);
         __syncthreads();
@@ -1047,14 +1051,14 @@ __global__ __launch_bounds__(BLOCK) void k_tile_order(const int* __restrict__ nt
 }
 
 // Deterministic mode: the sort keys of k_tile_rank, one wave per tile.
-__global__ __launch_bounds__(BLOCK) void k_tile_keys(const int* __restrict__ ntiles, Geo g, int offsets,
+__global__ __launch_bounds__(BLOCK) void k_tile_keys(const int* __restrict__ ntiles, Geo g, int offsets, int perkey,
                                                      const int* __restrict__ mstart, const int4* __restrict__ tiles,
                                                      int2* __restrict__ tbucket, const DevStats* __restrict__ st)
 {
     const int nw = (int)(gridDim.x * (BLOCK / 64)), n = *ntiles, W = st->W;
     for (int t = (int)((blockIdx.x * (int64_t)BLOCK + threadIdx.x) >> 6); t < n; t += nw) {
         const int4 tl = tiles[t];
-        const int bk = tile_bucket(tl, g, offsets, W, mstart);
+        const int bk = tile_bucket(tl, g, offsets, W, perkey, mstart);
         // sort key (descending): cost bucket, then ascending slice index
         if ((threadIdx.x & 63) == 0) tbucket[t] = make_int2(bk * SLICE_KEYS + (SLICE_KEYS - 1 - (tl.w >> 5)), 0);
     }
@@ -1777,8 +1781,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
     // Deterministic mode: a key's gradient is rounded to fixed point once per
     // tile, and pieces by queries would round it once each (65,028 points at 85^3:
     // the first moments' error against 64 bits 3.6e-5 instead of 3.3e-5), so the
-    // backward of a cut tile runs in a launch of its own (a.rest), cut by keys:
-    // 250,007 points at 27^3, tile kernels 364 us, 312 with both in one launch.
+    // backward of a cut tile runs in a launch of its own (a.rest), cut by keys.
     const bool later = MODE == MODE_FIT && lanes > 0 && a.gfix;
 
     if (MODE != MODE_GRAD) {
@@ -2205,15 +2208,20 @@ struct Items {
 
 // From the tiles per bucket, for a launch whose workgroups fill slots slots;
 // cut: the items of the cut tiles only.
-__device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bcount, int slots, bool cut, float* fsh,
-                                           int* ish)
+__device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bcount, int slots, float part, float least,
+                                           bool cut, float* fsh, int* ish)
 {
     const int i = threadIdx.x;
     const int cnt = i < 128 ? bcount[127 - i] : 0;
     const float cost = exp2f(0.25f * ((float)(127 - i) + 0.5f));
     const float total = block_sum(i < 128 ? (float)cnt * cost : 0.0f, fsh);
-    const float share = fmaxf(PIECE_SHARE * total / (float)slots, PIECE_LEAST);
-    const int k = cost > share ? (int)fminf(ceilf(cost / share), (float)MAX_PIECES) : 1;
+    const float share = fmaxf(part * total / (float)slots, least);
+    int k = cost > share ? (int)fminf(ceilf(cost / share), (float)MAX_PIECES) : 1;
+    if (cut) {  // the fair share of what is left
+        const float most = fmaxf(PIECE_SHARE * block_sum(k > 1 && i < 128 ? (float)cnt * cost : 0.0f, fsh) / (float)slots,
+                                 0.125f * least);
+        if (k > 1) k = (int)fminf(fmaxf(ceilf(cost / most), 2.0f), (float)MAX_KEY_PIECES);
+    }
     int tot;
     const int t0 = block_excl_scan(cnt, ish, &tot);
     const int f0 = block_excl_scan(i < 128 && (k > 1 || !cut) ? cnt * k : 0, ish, &tot);
@@ -2308,14 +2316,35 @@ __device__ __forceinline__ void item_priority(int item, int slots)
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// A workgroup's first item and the one after the item at hand (n or more:
+// none).  Up to one item per workgroup none asks the counter: 1024 atomics on one
+// address before the first item and as many behind the last took 27 us in a
+// launch with nothing to do, and a fit of 65,536 points at 8^3 131 us instead of
+// 113.  With more items all come from the counter, the first too, as the order in
+// which the workgroups arrive there spreads the heavy ones: taken by index, a fit of
+// 2^21 points at 32^3 took 1411 us instead of 1262.
+__device__ __forceinline__ int next_item(int* queue, int n, int& sh)
+{
+    if (n <= (int)gridDim.x) return n;
+    __syncthreads();
+    if (threadIdx.x == 0) sh = atomicAdd(queue, 1);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh);
+}
+
+__device__ __forceinline__ int first_item(int* queue, int n, int& sh)
+{
+    return n <= (int)gridDim.x ? (int)blockIdx.x : next_item(queue, n, sh);
+}
+
 __device__ __forceinline__ int4 uniform(const int4 v)
 {
     return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
                      __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
 }
 
-// Persistent tile kernel of one shape: workgroups pull items (heaviest
-// first) from an atomic queue until it is empty.
+// Persistent tile kernel of one shape: workgroups take items, heaviest first,
+// until there are none.
 // Degree 2 holds more live state per query and fits three waves per SIMD.
 template <int MODE, bool QGRAD, int DEG>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 ? 3 : 4, 8))) void k_tile(TileArgs a)
@@ -2325,16 +2354,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
     const int W = __builtin_amdgcn_readfirstlane(a.st->W);
     const float bmin2 = __uint_as_float(a.st->bmin_bits) * LOG2E;
     const bool rest = MODE == MODE_GRAD && a.rest;
-    plan_items(I, a.st->bcount, a.slots, rest, S.fsc, S.isc);
+    // a deterministic gradient call cuts as any other, the rest of a
+    // deterministic fit as that fit did
+    const bool det = a.gfix && (MODE == MODE_FIT || rest);
+    plan_items(I, a.st->bcount, a.slots, det ? DET_SHARE : PIECE_SHARE,
+               det ? DET_LEAST : (MODE == MODE_FIT ? FIT_LEAST : PIECE_LEAST), rest, S.fsc, S.isc);
     const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
     if (!rest && blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
     PairCount pc;
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) S.tile = atomicAdd(rest ? &a.st->bqueue : &a.st->queue, 1);
-        __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(S.tile);
-        if (item >= nitems) break;
+    int* queue = rest ? &a.st->bqueue : &a.st->queue;
+    for (int item = first_item(queue, nitems, S.tile); item < nitems; item = next_item(queue, nitems, S.tile)) {
         item_priority(item, a.slots);
         int j, k, lanes;
         int2 keys;
@@ -2377,16 +2406,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
 {
     __shared__ TileSmem<DEG> S;
     __shared__ Items I;
-    plan_items(I, gcount, slots, false, S.fsc, S.isc);
+    plan_items(I, gcount, slots, PIECE_SHARE, FIT_LEAST, false, S.fsc, S.isc);
     const int n = __builtin_amdgcn_readfirstlane(I.first[128]);
     PairCount pc;
     int cur = -1;  // shape whose pair counts pc holds
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) S.tile = atomicAdd(gqueue, 1);
-        __syncthreads();
-        const int t = __builtin_amdgcn_readfirstlane(S.tile);
-        if (t >= n) break;
+    for (int t = first_item(gqueue, n, S.tile); t < n; t = next_item(gqueue, n, S.tile)) {
         item_priority(t, slots);
         int j, k, lanes;
         int2 keys;
@@ -3117,11 +3141,12 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
                                                        (int)w.NK, w.ps, w.pv, mode == MODE_FIT ? nullptr : w.pidx);
     }
     const int* ntiles = w.tstart + w.NB3;
-    int64_t cgrid = (w.max_tiles + COST_TILES - 1) / COST_TILES;
+    const int perkey = mode == MODE_GRAD ? GRAD_PERKEY : 0;
+    int64_t cgrid = (w.max_tiles + BLOCK / 64 - 1) / (BLOCK / 64);
     if (cgrid > (int64_t)w.num_cu * 16) cgrid = (int64_t)w.num_cu * 16;
     if (!det) {
         k_make_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g, ps, w.cap, w.group, w.st, w.tstart + w.NB3, w.tiles_tmp);
-        k_tile_cost<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, w.mstart, w.tiles_tmp, w.tbucket, w.st);
+        k_tile_cost<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, perkey, w.mstart, w.tiles_tmp, w.tbucket, w.st);
         // the batched path orders all shapes' tiles together
         if (ordered)
             k_tile_order<<<grid_for(w.max_tiles), BLOCK, 0, s>>>(ntiles, w.tbucket, w.st, w.tiles_tmp, w.tiles);
@@ -3131,7 +3156,7 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
     hipError_t e = scan(w.btiles, w.NB3, w.scan_blk, w.tstart, s);
     if (e != hipSuccess) return e;
     k_build_tiles<<<grid_for(w.NB3), BLOCK, 0, s>>>(w.NB3, g, ps, w.cap, w.group, w.st, w.tstart, w.tiles_tmp);
-    k_tile_keys<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, w.mstart, w.tiles_tmp, w.tbucket, w.st);
+    k_tile_keys<<<(unsigned)cgrid, BLOCK, 0, s>>>(ntiles, g, p.offsets, perkey, w.mstart, w.tiles_tmp, w.tbucket, w.st);
     k_tile_rank<<<(unsigned)w.nch, BLOCK, 0, s>>>(ntiles, w.tbucket, (int)w.nch, w.chist, w.st);
     e = scan(w.chist, 128 * SLICE_KEYS * w.nch, w.scan_blk, w.cstart, s);
     if (e != hipSuccess) return e;
