@@ -31,11 +31,15 @@ constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
 // and 948 us over 524,288 points at 32^3, 14.3, 13.7 and 13.9 ms over 1,504,109 at 83^3.
 // Its backward's pieces, by keys, are up to MAX_KEY_PIECES per tile: a few tiles of
 // thousands of keys each are all that launch may have (16.4 ms with 8).
+// An eval without normals has the cheapest pairs and pays most for the cut: shares of
+// 0.75, 1.15 and 1.3 gave 228, 208 and 206 us over 547,596 points at 13^3 (219 uncut), 160,
+// 157 and 153 over 60,000 at 24^3; with normals 0.75, 1.0 and 1.3 gave 462, 488 and 643 us
+// over 300,007 at 32^3.
 // In a gradient call a key's gather, load and flush count as GRAD_PERKEY queries:
 // 2,093 points forward and backward at 56^3, most tiles one query and up to 28,000
 // keys, 779 us without and 577 with it.
 constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
-constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f;
+constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
 constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
 constexpr int GRAD_PERKEY = 32;
 constexpr int SLICE_KEYS = 8;   // slice-index sort keys per cost bucket in the tile order

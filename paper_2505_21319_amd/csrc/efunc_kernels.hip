@@ -2162,6 +2162,7 @@ __device__ __forceinline__ void tile_run(const TileArgs& a, TileSmem<DEG>& S, co
             }
             __syncthreads();
             // one atomic per key channel, NF consecutive lanes per key
+#pragma unroll 4
             for (int kf = tid / NF; kf < n; kf += BLOCK / NF) {
                 const int tg = S.kid[kf];
                 const bool mv = tg < 0;
@@ -2357,7 +2358,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
     // a deterministic gradient call cuts as any other, the rest of a
     // deterministic fit as that fit did
     const bool det = a.gfix && (MODE == MODE_FIT || rest);
-    plan_items(I, a.st->bcount, a.slots, det ? DET_SHARE : PIECE_SHARE,
+    plan_items(I, a.st->bcount, a.slots,
+               det ? DET_SHARE : (MODE == MODE_EVAL && !QGRAD ? EVAL_SHARE : PIECE_SHARE),
                det ? DET_LEAST : (MODE == MODE_FIT ? FIT_LEAST : PIECE_LEAST), rest, S.fsc, S.isc);
     const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
     if (!rest && blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
