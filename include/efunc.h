@@ -226,6 +226,13 @@ int efunc_fit_step_static(const efunc_config* cfg, float* theta, float* m, float
  * stream of that call.  Errors: EFUNC_EINVAL, EFUNC_EHIP. */
 int efunc_get_stats(efunc_ctx* ctx, efunc_stats* out);
 
+/* Work items of the last eval / grad / fit_step / loss_grad on a context (host
+ * array): items[0] of its tile kernel, which cuts tiles that are heavy for
+ * their call into several; items[1] of the backward of a deterministic fit's
+ * cut tiles (0 in other calls).  Synchronises the stream of that call.
+ * Errors: EFUNC_EINVAL, EFUNC_EHIP. */
+int efunc_get_items(efunc_ctx* ctx, int64_t items[2]);
+
 /* Instrumentation.  With timing enabled, every eval/grad/fit_step call
  * records a pair of HIP events around its tile kernel (the kernel that
  * evaluates the key-query pairs) on the call's stream, for up to 4096 calls.

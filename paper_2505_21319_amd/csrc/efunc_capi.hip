@@ -742,6 +742,22 @@ int efunc_get_stats(efunc_ctx* ctx, efunc_stats* out)
     return EFUNC_OK;
 }
 
+int efunc_get_items(efunc_ctx* ctx, int64_t items[2])
+{
+    g_err.clear();
+    int rc;
+    if ((rc = check_ctx(ctx))) return rc;
+    if (!items) return fail(EFUNC_EINVAL, "items is NULL");
+    DevStats st;
+    hipStream_t s = ctx->last_stream;
+    hipError_t e = hipMemcpyAsync(&st, ctx->w.st, sizeof(st), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "item count readback");
+    items[0] = st.nitems;
+    items[1] = st.nrest;
+    return EFUNC_OK;
+}
+
 int efunc_set_timing(efunc_ctx* ctx, int32_t enable)
 {
     g_err.clear();

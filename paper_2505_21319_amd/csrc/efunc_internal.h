@@ -58,7 +58,8 @@ struct DevStats {
     int W;                    // window half-width of this call
     int nonfinite;            // non-finite parameters seen by the key preparation
     int nitems;               // work items of the tile kernel
-    int pad0[27];
+    int nrest;                // and of the backward of a deterministic fit's cut tiles
+    int pad0[26];
     int queue;                // tile work-queue head
     int bqueue;               // that of the backward of a deterministic fit's cut tiles
     int pad1[30];

@@ -135,6 +135,8 @@ __global__ void k_reset_front(DevStats* st, int* __restrict__ ntiles, int* __res
         st->nfb = 0;
         st->fbqueue = 0;
         st->nonfinite = 0;
+        st->nitems = 0;
+        st->nrest = 0;
         st->pairs = 0ull;
         st->pairs_moved = 0ull;
         st->bwd_pairs = 0ull;
@@ -2378,7 +2380,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
                det ? DET_SHARE : (MODE == MODE_EVAL && !QGRAD ? EVAL_SHARE : PIECE_SHARE),
                det ? DET_LEAST : (MODE == MODE_FIT ? FIT_LEAST : PIECE_LEAST), rest, S.fsc, S.isc);
     const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
-    if (!rest && blockIdx.x == 0 && threadIdx.x == 0) a.st->nitems = nitems;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *(rest ? &a.st->nrest : &a.st->nitems) = nitems;
     PairCount pc;
     int* queue = rest ? &a.st->bqueue : &a.st->queue;
     for (int item = first_item(queue, nitems, S.tile); item < nitems; item = next_item(queue, nitems, S.tile)) {

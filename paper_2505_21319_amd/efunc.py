@@ -68,6 +68,7 @@ class efunc_stats(C.Structure):
 # every symbol declared in include/efunc.h
 EXPORTS = ["efunc_default_config", "efunc_channels", "efunc_default_adam", "efunc_create", "efunc_destroy",
            "efunc_init_params", "efunc_eval", "efunc_grad", "efunc_fit_step", "efunc_get_stats",
+           "efunc_get_items",
            "efunc_set_timing", "efunc_read_timing", "efunc_default_tuning", "efunc_set_tuning",
            "efunc_get_tuning", "efunc_batch_create", "efunc_batch_destroy", "efunc_batch_bind",
            "efunc_batch_fit", "efunc_batch_set_tuning", "efunc_batch_get_tuning",
@@ -103,6 +104,7 @@ def lib() -> C.CDLL:
         L.efunc_grad.argtypes = [vp, vp, vp, vp, vp, vp, i64, vp, vp]
         L.efunc_fit_step.argtypes = [vp, vp, vp, vp, i64, C.POINTER(efunc_adam), vp, vp, i64, vp, vp]
         L.efunc_get_stats.argtypes = [vp, C.POINTER(efunc_stats)]
+        L.efunc_get_items.argtypes = [vp, C.POINTER(i64)]
         L.efunc_set_timing.argtypes = [vp, C.c_int32]
         L.efunc_read_timing.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
         L.efunc_default_tuning.argtypes = [C.POINTER(efunc_tuning)]
@@ -140,7 +142,7 @@ def lib() -> C.CDLL:
         L.efunc_last_error.argtypes = []
         L.efunc_last_error.restype = C.c_char_p
         for name in ("efunc_create", "efunc_destroy", "efunc_init_params", "efunc_eval",
-                     "efunc_grad", "efunc_fit_step", "efunc_get_stats", "efunc_set_timing",
+                     "efunc_grad", "efunc_fit_step", "efunc_get_stats", "efunc_get_items", "efunc_set_timing",
                      "efunc_read_timing", "efunc_set_tuning", "efunc_get_tuning",
                      "efunc_batch_create", "efunc_batch_destroy", "efunc_batch_bind",
                      "efunc_batch_fit", "efunc_batch_set_tuning", "efunc_batch_get_tuning",
@@ -306,6 +308,13 @@ def efunc_get_stats(ctx) -> dict:
     s = efunc_stats()
     _check(lib().efunc_get_stats(ctx, C.byref(s)))
     return s.as_dict()
+
+
+def efunc_get_items(ctx) -> tuple:
+    """(work items of the last call's tile kernel, of its cut tiles' backward)."""
+    n = (C.c_int64 * 2)()
+    _check(lib().efunc_get_items(ctx, n))
+    return int(n[0]), int(n[1])
 
 
 def efunc_set_timing(ctx, enable: bool) -> None:
@@ -615,6 +624,9 @@ class Engine:
 
     def stats(self):
         return efunc_get_stats(self.ctx)
+
+    def items(self):
+        return efunc_get_items(self.ctx)
 
     def set_tuning(self, tile_cap=512, group_cells=2, blocks_per_cu=8):
         efunc_set_tuning(self.ctx, efunc_tuning(tile_cap, group_cells, blocks_per_cu))

@@ -1,0 +1,132 @@
+"""Cut tiles of every model: one lattice cell holds P queries and a window of
+hundreds or thousands of keys, so that its tile is cut in every call (asserted
+from the library's count of work items).  Degrees 0 and 2, grid keys alone,
+moved keys alone (whose reference exponent is an exact maximum), a fixed scale,
+and a forced window that certifies only part of the crowded cell's queries, so
+that the others fall back to all keys while the tile's pieces run.  Values, lse,
+query gradients, parameter gradients and a fit step, plain and deterministic,
+against the FP64 variant oracle under the global definition, with the tolerances
+of tests/parity.py."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import variants as V
+from tests import parity as PT
+from tests.test_oracle_var_pins import random_theta
+
+# (name, degree, grid_keys, moved_keys, learn_scale, R, P, cell, rho, forced window)
+CASES = [
+    ("f0_both", 0, 1, 1, 1, 10, 400, 4, (1.5, 2.5), 0),
+    ("f2_both", 2, 1, 1, 1, 10, 512, 4, (1.5, 2.5), 0),
+    ("f2_both_few", 2, 1, 1, 1, 18, 33, 8, (1.5, 2.5), 0),
+    ("f2_grid", 2, 1, 0, 1, 12, 300, 5, (1.5, 2.5), 0),
+    ("f1_moved", 1, 0, 1, 1, 12, 512, 5, (1.5, 2.5), 0),
+    ("f1_moved_few", 1, 0, 1, 1, 18, 60, 8, (1.5, 2.5), 0),
+    ("f2_moved_fixed", 2, 0, 1, 0, 12, 512, 5, (2.0, 2.0), 0),
+    ("f1_fallback", 1, 1, 1, 1, 14, 450, 6, (3.8, 4.0), 4),
+    ("f2_fallback", 2, 1, 1, 1, 14, 450, 6, (3.8, 4.0), 4),
+    ("f1_moved_fallback", 1, 0, 1, 1, 14, 450, 6, (3.8, 4.0), 4),
+]
+
+
+@pytest.fixture(scope="module")
+def E():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2505_21319_amd import efunc
+    efunc.lib()
+    V.build_var_oracle(force=False)
+    return efunc
+
+
+def test_item_counts_reject_null():
+    from paper_2505_21319_amd import efunc as B
+    n = (ctypes.c_int64 * 2)()
+    assert B.lib().efunc_get_items(None, n) == B.EFUNC_EINVAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("det", [0, 1])
+@pytest.mark.parametrize("c", CASES, ids=[c[0] for c in CASES])
+def test_cut_tiles_of_every_model(E, c, det):
+    name, deg, grid, moved, learn, R, P, cell, rho, window = c
+    m = V.Model(R=R, degree=deg, grid_keys=grid, moved_keys=moved, learn_scale=learn, rho_fixed=rho[0])
+    th = random_theta(m, 11 + R, rho=rho, offset=0.35)
+    n, nch = th.size, V.channels(m)
+    rng = np.random.default_rng(P + R)
+    h = 2.0 / (R - 1)
+    q = (-1.0 + cell * h + h * rng.uniform(0.02, 0.98, (P, 3))).astype(np.float32)
+    o = (np.linalg.norm(q, axis=1) - 0.5).astype(np.float32)
+    keys = V.build_keys(m, th)
+    O, lse, sig = V.eval_global(keys, deg, q)
+    kap, tail = V.eval_cond(keys, deg, q, PT.T_TAIL, with_tail=True)
+    ref = dict(O=O, lse=lse, sigma=sig, kappa=kap, tail=tail)
+    dl = (2 * (O - o) / P).astype(np.float32)
+    fr = V.fit_step(m, th, np.zeros(n), np.zeros(n), 1, q, o)
+    gk, ak, bk = V.grad_global(keys, deg, q, dl.astype(np.float64), T=PT.T_TAIL)
+    gr, ar, br = (V.grad_theta(m, th, x) for x in (gk, ak, bk))
+
+    cfg = dict(degree=deg, grid_keys=grid, offsets=moved, learn_scale=learn, rho_fixed=rho[0], window=window,
+               deterministic=det)
+    with E.Engine(R, P, **cfg) as eng:
+        def cut(rest=False):
+            st, items = eng.stats(), eng.items()
+            assert items[0] > st["n_tiles"] and (items[1] > 1) == rest, (items, st)
+            assert 0 < st["n_uncertified"] < P if window else st["n_uncertified"] == 0, st
+
+        t, tq, to = PT.to_dev(th), PT.to_dev(q), PT.to_dev(o)
+        for normals in (False, True):
+            Og, lg, dq, _ = eng.eval(t, tq, with_qgrad=normals)
+            cut()
+            PT.check_eval(Og.cpu().numpy(), lg.cpu().numpy(), ref)
+        PT.check_qgrad(dq.cpu().numpy(), PT.qgrad_reference(keys, q, degree=deg))
+        G = eng.grad(t, tq, PT.to_dev(O), PT.to_dev(lse), PT.to_dev(dl))
+        cut()
+        PT.check_grad(G.cpu().numpy(), gr, ar, br, nch=nch)
+        mom, v = torch.zeros(n, device=PT.DEV), torch.zeros(n, device=PT.DEV)
+        loss = torch.zeros(2, device=PT.DEV, dtype=torch.float64)
+        eng.fit_step(t, mom, v, 1, tq, to, loss)
+        cut(rest=bool(det))
+        loss = loss.cpu().numpy()
+        assert abs(loss[0] - fr["loss"]) <= 1e-5 * fr["loss"] and abs(loss[1] - fr["l1"]) <= 1e-5 * fr["l1"]
+        PT.check_grad(mom.cpu().numpy().astype(np.float64) / (1.0 - np.float32(0.9)), fr["grad"], ar, br, nch=nch)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("c", [c for c in CASES if not c[9]], ids=[c[0] for c in CASES if not c[9]])
+def test_cut_tiles_of_every_model_in_a_batch(E, c):
+    """The same crowded cells as shapes of a batch, whose tiles are cut by the
+    same rule; direct launches and replays of the captured iteration."""
+    name, deg, grid, moved, learn, R, P, cell, rho, _ = c
+    m = V.Model(R=R, degree=deg, grid_keys=grid, moved_keys=moved, learn_scale=learn, rho_fixed=rho[0])
+    th = random_theta(m, 11 + R, rho=rho, offset=0.35)
+    n, nch = th.size, V.channels(m)
+    rng = np.random.default_rng(P + R)
+    h = 2.0 / (R - 1)
+    q = (-1.0 + cell * h + h * rng.uniform(0.02, 0.98, (P, 3))).astype(np.float32)
+    o = (np.linalg.norm(q, axis=1) - 0.5).astype(np.float32)
+    keys = V.build_keys(m, th)
+    fr = V.fit_step(m, th, np.zeros(n), np.zeros(n), 1, q, o)
+    _, ak, bk = V.grad_global(keys, deg, q, 2 * (fr["O"] - o) / P, T=PT.T_TAIL)
+    ar, br = V.grad_theta(m, th, ak), V.grad_theta(m, th, bk)
+    tq, to = PT.to_dev(q), PT.to_dev(o)
+    adam = E.efunc_default_adam()
+    adam.lr = 0.0  # the second iteration meets the same parameters
+    for use_graph in (False, True):
+        mb, vb = ([torch.zeros(n, device=PT.DEV) for _ in range(2)] for _ in range(2))
+        lb = torch.zeros(2, 2, device=PT.DEV, dtype=torch.float64)
+        with E.BatchEngine([R, R], [P, P], degree=deg, grid_keys=grid, offsets=moved, learn_scale=learn,
+                           rho_fixed=rho[0]) as b:
+            b.bind([PT.to_dev(th).reshape(-1) for _ in range(2)], mb, vb, [tq, tq], [to, to], lb)
+            for _ in range(2):
+                for x in mb:
+                    x.zero_()
+                b.fit(1, 1, use_graph=use_graph, adam=adam)
+                torch.cuda.synchronize()
+                for s in range(2):
+                    loss = lb[s].cpu().numpy()
+                    assert abs(loss[0] - fr["loss"]) <= 1e-5 * fr["loss"] and abs(loss[1] - fr["l1"]) <= 1e-5 * fr["l1"]
+                    g = mb[s].cpu().numpy().astype(np.float64) / (1.0 - np.float32(0.9))
+                    PT.check_grad(g, fr["grad"], ar, br, nch=nch)
