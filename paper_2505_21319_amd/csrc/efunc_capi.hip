@@ -155,7 +155,7 @@ size_t carve_work(const efunc_config& cfg, const Layout& layout, int64_t max_poi
     // sort's counts, which are no longer read when it runs; cutting heavy
     // tiles adds at most 1 / PIECE_SHARE items per workgroup slot
     {
-        const int64_t extra = (int64_t)(1.25 / PIECE_SHARE * (4.0 * w.num_cu)) + 1, cut = (MAX_PIECES - 1) * w.max_tiles;
+        const int64_t extra = (int64_t)(1.25 / PIECE_SHARE * TILE_SLOTS * w.num_cu) + 1, cut = (MAX_PIECES - 1) * w.max_tiles;
         const int64_t items = w.max_tiles + (extra < cut ? extra : cut);
         const int64_t words = 2 * nkeys + 1 > 4 * items ? 2 * nkeys + 1 : 4 * items;
         k.take(w.chist, words);

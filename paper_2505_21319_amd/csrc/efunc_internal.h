@@ -42,6 +42,15 @@ constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
 constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
 constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
 constexpr int GRAD_PERKEY = 32;
+// Workgroups among which the cut shares a launch's work: those that run at a time,
+// four per CU or as many as the tuning launches.  (A CU holds three of degree 2;
+// with 3 instead of 4 there, hence coarser cuts, a fit of 444,586 points at 27^3
+// took 668 us instead of 612, one of 100,000 at 75^3 5.05 ms instead of 5.20.)
+constexpr int TILE_SLOTS = 4;
+inline int tile_slots(int num_cu, int blocks_per_cu)
+{
+    return num_cu * (blocks_per_cu < TILE_SLOTS ? blocks_per_cu : TILE_SLOTS);
+}
 constexpr int SLICE_KEYS = 8;   // slice-index sort keys per cost bucket in the tile order
 constexpr int RS_TILE = 4 * BLOCK;  // elements per workgroup of the deterministic radix sort
 constexpr float LOG2E = 1.4426950408889634f;
@@ -163,7 +172,7 @@ struct Work {
     float4* pv;           // [max_points] {O, lse, 0, 0} (backward inputs)
     int* pidx;            // [max_points] original query index
     int* fb;              // [max_points] fallback list (sorted query positions)
-    double2* lpart;       // [max_tiles + extra_items]  per-item loss sums (overlies chist and cstart)
+    double2* lpart;       // [max_tiles + what the cut adds]  per-item loss sums (overlies chist and cstart)
     int* scan_blk;        // [ceil(max(8 NB3 PSPLIT, 128 SLICE_KEYS nch) / SCAN_TILE) + 1] scan block sums
     float* grad;          // [nch I] internal gradient of efunc_fit_step (kept zero)
     float* gslot;         // [nfl I] moved keys' gradient by binned record, flush-slot order (kept zero)
@@ -229,7 +238,7 @@ struct TileArgs {
     float4* pv;
     const int* pidx;
     const int4* tiles;
-    int slots;          // workgroups that run at a time
+    int slots;          // workgroups among which the cut shares the work (see tile_slots)
     int* fb;
     double2* lpart;
     DevStats* st;

@@ -3199,7 +3199,7 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered)
     a.pv = w.pv;
     a.pidx = w.pidx;
     a.tiles = ordered ? w.tiles : w.tiles_tmp;
-    a.slots = 4 * w.num_cu;
+    a.slots = tile_slots(w.num_cu, w.bpc);
     a.fb = w.fb;
     a.lpart = w.lpart;
     a.st = w.st;
@@ -3294,7 +3294,8 @@ template <int DEG>
 static void launch_batch(const TileArgs* tab, int S, const int2* gtiles, const int* gcount, int* gqueue,
                          int grid, int fgrid, hipEvent_t ev_stop, hipStream_t s)
 {
-    k_tile_batch<DEG><<<grid, BLOCK, 0, s>>>(tab, gtiles, gcount, 4 * fgrid, gqueue);
+    const int slots = grid < TILE_SLOTS * fgrid ? grid : TILE_SLOTS * fgrid;  // fgrid: one per CU
+    k_tile_batch<DEG><<<grid, BLOCK, 0, s>>>(tab, gtiles, gcount, slots, gqueue);
     if (ev_stop) (void)hipEventRecord(ev_stop, s);
     k_fallback_batch<DEG><<<fgrid, FB_BLOCK, 0, s>>>(tab, S);
 }

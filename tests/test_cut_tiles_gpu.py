@@ -130,3 +130,54 @@ def test_cut_tiles_of_every_model_in_a_batch(E, c):
                     assert abs(loss[0] - fr["loss"]) <= 1e-5 * fr["loss"] and abs(loss[1] - fr["l1"]) <= 1e-5 * fr["l1"]
                     g = mb[s].cpu().numpy().astype(np.float64) / (1.0 - np.float32(0.9))
                     PT.check_grad(g, fr["grad"], ar, br, nch=nch)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("det", [0, 1])
+def test_cut_shares_the_work_among_the_launched_workgroups(E, det):
+    """Equal tiles, two or more per CU: with the default tuning each is above the
+    share of one of four workgroups per CU, with one workgroup per CU all are
+    below its share and stay whole.  The fits agree either way."""
+    R, P, tiles = 18, 40, 600
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert 2 * cus <= tiles <= 3 * cus
+    th = random_theta(V.Model(R=R), 3, rho=(1.5, 2.5), offset=0.35)
+    rng = np.random.default_rng(det)
+    h = 2.0 / (R - 1)
+    cells = rng.permutation((R - 1) ** 3)[:tiles]
+    corner = np.stack([cells // (R - 1) ** 2, cells // (R - 1) % (R - 1), cells % (R - 1)], 1)
+    q = (-1.0 + h * (corner[:, None, :] + rng.uniform(0.05, 0.95, (tiles, P, 3)))).reshape(-1, 3).astype(np.float32)
+    o = (np.linalg.norm(q, axis=1) - 0.5).astype(np.float32)
+    t, tq, to = PT.to_dev(th), PT.to_dev(q), PT.to_dev(o)
+    dl = PT.to_dev(rng.standard_normal(len(q)) / len(q))
+    moms, values = [], []
+    with E.Engine(R, len(q), deterministic=det) as eng:
+        for bpc in (8, 1):
+            eng.set_tuning(group_cells=0, blocks_per_cu=bpc)
+
+            def check():
+                items = eng.items()
+                assert eng.stats()["n_tiles"] == tiles
+                assert items[0] > tiles if bpc == 8 else items == (tiles, 0), (bpc, items)
+
+            O, lse, _, _ = eng.eval(t, tq)
+            check()
+            eng.eval(t, tq, with_qgrad=True)
+            check()
+            eng.grad(t, tq, O, lse, dl)
+            check()
+            mom, v = torch.zeros(th.size, device=PT.DEV), torch.zeros(th.size, device=PT.DEV)
+            adam = E.efunc_default_adam()
+            adam.lr = 0.0
+            eng.fit_step(t, mom, v, 1, tq, to, None, adam)
+            check()
+            moms.append(mom.cpu().numpy())
+            values.append(O.cpu().numpy())
+    scale = np.abs(moms[0].reshape(-1, 13)).max(axis=0)
+    assert np.all(np.abs(moms[0] - moms[1]).reshape(-1, 13) <= 1e-4 * np.abs(moms[0]).reshape(-1, 13) + 1e-5 * scale)
+    keys = V.build_keys(V.Model(R=R), th)
+    s = slice(0, len(q), 97)
+    O, _, sig = V.eval_global(keys, 1, q[s])
+    kap, tail = V.eval_cond(keys, 1, q[s], PT.T_TAIL, with_tail=True)
+    for x in values:
+        PT.check_values(x[s], O, sig, kappa=kap, tail=tail)
