@@ -37,11 +37,18 @@ constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
 // over 300,007 at 32^3.
 // In a gradient call a key's gather, load and flush count as GRAD_PERKEY queries:
 // 2,093 points forward and backward at 56^3, most tiles one query and up to 28,000
-// keys, 779 us without and 577 with it.
+// keys, 779 us without and 577 with it.  In a fit they count as FIT_PERKEY: tiles of
+// one or two queries and thousands of keys cost about as much as their gathers, and
+// left out of the sum they made the share so small that the denser tiles were cut,
+// each piece gathering all keys again.  Without and with: 60,000 points at 100^3 7309
+// and 6853 us (6901 uncut), 553,527 near the surface at 12^3 311 and 260, 250,007 of
+// degree 2 at 32^3 647 and 611.  Over 108 fits of 4^3 to 100^3, 8, 16 and 24 gave 0.8,
+// 1.2 and 0.8 % in the mean and cost at worst 10, 5 and 14.  A deterministic fit cuts
+// its backward by keys and keeps 0: 972,595 points at 38^3 1439 us, with 16 1818.
 constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
 constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
 constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
-constexpr int GRAD_PERKEY = 32;
+constexpr int GRAD_PERKEY = 32, FIT_PERKEY = 16;
 // Workgroups among which the cut shares a launch's work: those that run at a time,
 // four per CU or as many as the tuning launches.  (A CU holds three of degree 2;
 // with 3 instead of 4 there, hence coarser cuts, a fit of 444,586 points at 27^3

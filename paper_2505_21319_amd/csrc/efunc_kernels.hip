@@ -3161,7 +3161,7 @@ hipError_t run_front(const Work& w, const Problem& p, Mode mode, bool ordered, h
                                                        (int)w.NK, w.ps, w.pv, mode == MODE_FIT ? nullptr : w.pidx);
     }
     const int* ntiles = w.tstart + w.NB3;
-    const int perkey = mode == MODE_GRAD ? GRAD_PERKEY : 0;
+    const int perkey = mode == MODE_GRAD ? GRAD_PERKEY : (mode == MODE_FIT && !det ? FIT_PERKEY : 0);
     int64_t cgrid = (w.max_tiles + BLOCK / 64 - 1) / (BLOCK / 64);
     if (cgrid > (int64_t)w.num_cu * 16) cgrid = (int64_t)w.num_cu * 16;
     if (!det) {

@@ -181,3 +181,29 @@ def test_cut_shares_the_work_among_the_launched_workgroups(E, det):
     kap, tail = V.eval_cond(keys, 1, q[s], PT.T_TAIL, with_tail=True)
     for x in values:
         PT.check_values(x[s], O, sig, kappa=kap, tail=tail)
+
+
+@pytest.mark.gpu
+def test_cut_of_a_fit_counts_the_gather_of_its_keys(E):
+    """A lattice of tiles of one query, each with every key in its window, and one
+    tile of 40: its pieces would gather the window's keys again for a share of the
+    work that the small tiles' own gathers outweigh, so a fit leaves it whole."""
+    R, P = 26, 40
+    th = random_theta(V.Model(R=R), 4, rho=(1.5, 2.5), offset=0.35)
+    rng = np.random.default_rng(1)
+    h = 2.0 / (R - 1)
+    c = np.stack(np.meshgrid(*[np.arange(R - 1)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    crowd = np.full((P, 3), 12)
+    q = (-1.0 + h * (np.concatenate([c, crowd]) + rng.uniform(0.05, 0.95, (len(c) + P, 3)))).astype(np.float32)
+    o = (np.linalg.norm(q, axis=1) - 0.5).astype(np.float32)
+    t, tq, to = PT.to_dev(th), PT.to_dev(q), PT.to_dev(o)
+    with E.Engine(R, len(q)) as eng:
+        eng.set_tuning(group_cells=0)
+        mom, v = torch.zeros(th.size, device=PT.DEV), torch.zeros(th.size, device=PT.DEV)
+        loss = torch.zeros(2, device=PT.DEV, dtype=torch.float64)
+        O, _, _, _ = eng.eval(t, tq)
+        eng.fit_step(t, mom, v, 1, tq, to, loss)
+        st = eng.stats()
+        assert st["W"] >= R - 2 and st["n_tiles"] == len(c) and eng.items() == (len(c), 0), (st, eng.items())
+        mse = float(((O - to).double() ** 2).mean())
+        assert abs(float(loss[0]) - mse) <= 1e-5 * mse
