@@ -179,7 +179,7 @@ struct Work {
     float4* pv;           // [max_points] {O, lse, 0, 0} (backward inputs)
     int* pidx;            // [max_points] original query index
     int* fb;              // [max_points] fallback list (sorted query positions)
-    double2* lpart;       // [max_tiles + what the cut adds]  per-item loss sums (overlies chist and cstart)
+    double2* lpart;       // [max_tiles + what the cut adds]  per-item loss sums (overlies pcount, or chist and cstart)
     int* scan_blk;        // [ceil(max(8 NB3 PSPLIT, 128 SLICE_KEYS nch) / SCAN_TILE) + 1] scan block sums
     float* grad;          // [nch I] internal gradient of efunc_fit_step (kept zero)
     float* gslot;         // [nfl I] moved keys' gradient by binned record, flush-slot order (kept zero)
