@@ -153,10 +153,10 @@ size_t carve_work(const efunc_config& cfg, const Layout& layout, int64_t max_poi
     k.take(w.tbucket, w.max_tiles);
     // The loss sums of the tile kernel's items take the place of counts that are no
     // longer read when it runs: of the queries' (pcount) where these hold as many,
-    // else of the tile sort's.  Cutting heavy tiles adds at most 1 / PIECE_SHARE
+    // else of the tile sort's.  Cutting heavy tiles adds at most 1 / FIT_SHARE
     // items per workgroup slot.
     {
-        const int64_t extra = (int64_t)(1.25 / PIECE_SHARE * TILE_SLOTS * w.num_cu) + 1, cut = (MAX_PIECES - 1) * w.max_tiles;
+        const int64_t extra = (int64_t)(1.25 / FIT_SHARE * TILE_SLOTS * w.num_cu) + 1, cut = (MAX_PIECES - 1) * w.max_tiles;
         const int64_t items = w.max_tiles + (extra < cut ? extra : cut);
         const bool fits = w.NK * PSPLIT >= 4 * items;
         const int64_t words = fits || 2 * nkeys + 1 > 4 * items ? 2 * nkeys + 1 : 4 * items;

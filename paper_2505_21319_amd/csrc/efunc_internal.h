@@ -45,8 +45,11 @@ constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
 // degree 2 at 32^3 647 and 611.  Over 108 fits of 4^3 to 100^3, 8, 16 and 24 gave 0.8,
 // 1.2 and 0.8 % in the mean and cost at worst 10, 5 and 14.  A deterministic fit cuts
 // its backward by keys and keeps 0: 972,595 points at 38^3 1439 us, with 16 1818.
+// With the gathers counted a fit takes FIT_SHARE: over 78 fits of 60,000 to 400,000
+// points at 24^3 to 80^3 0.75, 0.6, 0.5 and 0.4 gave 3.2, 3.4, 2.0 and -1.1 % over not
+// counting them and cost at worst 18, 3, 7 and 10.  In a batch 0.75 and 0.6 lie within 1 %.
 constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
-constexpr float PIECE_SHARE = 0.75f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
+constexpr float PIECE_SHARE = 0.75f, FIT_SHARE = 0.6f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
 constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
 constexpr int GRAD_PERKEY = 32, FIT_PERKEY = 16;
 // Workgroups among which the cut shares a launch's work: those that run at a time,

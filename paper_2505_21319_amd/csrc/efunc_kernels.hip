@@ -2377,7 +2377,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(DEG == 2 
     // deterministic fit as that fit did
     const bool det = a.gfix && (MODE == MODE_FIT || rest);
     plan_items(I, a.st->bcount, a.slots,
-               det ? DET_SHARE : (MODE == MODE_EVAL && !QGRAD ? EVAL_SHARE : PIECE_SHARE),
+               det ? DET_SHARE
+                   : (MODE == MODE_FIT ? FIT_SHARE : (MODE == MODE_EVAL && !QGRAD ? EVAL_SHARE : PIECE_SHARE)),
                det ? DET_LEAST : (MODE == MODE_FIT ? FIT_LEAST : PIECE_LEAST), rest, S.fsc, S.isc);
     const int nitems = __builtin_amdgcn_readfirstlane(I.first[128]);
     if (blockIdx.x == 0 && threadIdx.x == 0) *(rest ? &a.st->nrest : &a.st->nitems) = nitems;
