@@ -2234,6 +2234,7 @@ __device__ __forceinline__ void plan_items(Items& I, const int* __restrict__ bco
     const int cnt = i < 128 ? bcount[127 - i] : 0;
     const float cost = exp2f(0.25f * ((float)(127 - i) + 0.5f));
     const float total = block_sum(i < 128 ? (float)cnt * cost : 0.0f, fsh);
+    if (block_max(cnt ? cost : 0.0f, fsh) * (float)slots <= EVEN * total) least *= 2.0f;
     const float share = fmaxf(part * total / (float)slots, least);
     int k = cost > share ? (int)fminf(ceilf(cost / share), (float)MAX_PIECES) : 1;
     if (cut) {  // the fair share of what is left

@@ -138,7 +138,7 @@ def test_cut_shares_the_work_among_the_launched_workgroups(E, det):
     """Equal tiles, two or more per CU: with the default tuning each is above the
     share of one of four workgroups per CU, with one workgroup per CU all are
     below its share and stay whole.  The fits agree either way."""
-    R, P, tiles = 18, 40, 600
+    R, P, tiles = 18, 60, 600
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert 2 * cus <= tiles <= 3 * cus
     th = random_theta(V.Model(R=R), 3, rho=(1.5, 2.5), offset=0.35)
@@ -205,5 +205,35 @@ def test_cut_of_a_fit_counts_the_gather_of_its_keys(E):
         eng.fit_step(t, mom, v, 1, tq, to, loss)
         st = eng.stats()
         assert st["W"] >= R - 2 and st["n_tiles"] == len(c) and eng.items() == (len(c), 0), (st, eng.items())
+        mse = float(((O - to).double() ** 2).mean())
+        assert abs(float(loss[0]) - mse) <= 1e-5 * mse
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("det", [0, 1])
+def test_even_launches_keep_small_tiles_whole(E, det):
+    """A dense lattice of about equal tiles, two to four per CU, each up to twice the
+    floor of the cut: no tile outlasts the others, so the eval and the fit leave all
+    of them whole."""
+    R, P = 11, 250
+    th = random_theta(V.Model(R=R), 5, rho=(4.6, 5.4), offset=0.3)
+    rng = np.random.default_rng(2)
+    h = 2.0 / (R - 1)
+    c = np.stack(np.meshgrid(*[np.arange(R - 1)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+    q = (-1.0 + h * (c + rng.uniform(0.05, 0.95, (len(c), P, 3)))).reshape(-1, 3).astype(np.float32)
+    o = (np.linalg.norm(q, axis=1) - 0.5).astype(np.float32)
+    t, tq, to = PT.to_dev(th), PT.to_dev(q), PT.to_dev(o)
+    with E.Engine(R, len(q), deterministic=det) as eng:
+        eng.set_tuning(group_cells=0)
+        mom, v = torch.zeros(th.size, device=PT.DEV), torch.zeros(th.size, device=PT.DEV)
+        loss = torch.zeros(2, device=PT.DEV, dtype=torch.float64)
+        O, _, _, _ = eng.eval(t, tq, with_qgrad=True)
+        st = eng.stats()
+        assert eng.items() == (len(c), 0), eng.items()
+        # the premise: window keys times queries about the floor of an eval in the mean
+        # (and up to 1.4 times that, away from the lattice's faces)
+        assert st["n_tiles"] == len(c) and 0.9e5 < st["window_keys"] / len(c) * P < 1.1e5, st
+        eng.fit_step(t, mom, v, 1, tq, to, loss)
+        assert eng.items() == (len(c), 0), eng.items()
         mse = float(((O - to).double() ** 2).mean())
         assert abs(float(loss[0]) - mse) <= 1e-5 * mse
