@@ -2898,7 +2898,10 @@ __global__ void k_step_advance(int64_t* step)
 // idle.  Bound by the FP64 vector ALU: the exponential and the sums take some
 // 50 operations a sample, so a sample whose weight is nothing at all vertices
 // of a wave is passed over on a float32 distance: weights below e^-cut, cut =
-// ln(Ns) + 38, add up to less than 2^-53 of the sum.  16,384 samples, before (a
+// ln(Ns) + 38, add up to less than 2^-53 of the sum.  Their samples may lie far away:
+// the largest share in the mean, sqrt(cut / bw) e^-cut, is kept below 2^-53 of the
+// lattice's width by a cut larger by the log of that distance in widths (none at the
+// usual bandwidths).  16,384 samples, before (a
 // thread per vertex over all samples: 128 of the chip's 1024 SIMDs at 32^3) and
 // now: 32^3 vertices 1814 and 740 us, 17^3 1791 and 243 us, 8^3 1781 and 51 us.
 // 64 vertices share a sample's test and load; 16 at 32^3 take 988 us.
@@ -3370,7 +3373,8 @@ hipError_t run_init_params(const Work& w, const Geo& g, const Layout& L, float* 
     const auto blocks = [&](int x, int y, int z) {
         return (unsigned)((g.R + x - 1) / x) * ((g.R + y - 1) / y) * ((g.R + z - 1) / z);
     };
-    const float cut = (float)(log((double)(Ns > 1 ? Ns : 1)) + 38.0);
+    const double reach = log(sqrt(40.0 / (double)bandwidth) / ((double)g.hi - (double)g.lo));
+    const float cut = (float)(log((double)(Ns > 1 ? Ns : 1)) + 38.0 + (reach > 0.0 ? reach : 0.0));
     // a workgroup per CU at least, where smaller blocks can give it
     if (w.I >= 64 * (int64_t)w.num_cu)
         k_init_params<64><<<blocks(4, 4, 4), IP_BLOCK, 0, s>>>(theta, g, L, surf, Ns, (double)bandwidth, rho0, cut);
