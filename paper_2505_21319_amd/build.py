@@ -17,6 +17,8 @@ HIPCC_FLAGS = [
     # packed FP32 instructions are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
+    # a loop transformation that a pragma asks for and the compiler refuses
+    "-Werror=pass-failed",
 ]
 
 

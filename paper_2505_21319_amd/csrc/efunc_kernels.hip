@@ -19,6 +19,7 @@
 #include "efunc_internal.h"
 
 #include <math.h>
+#include <type_traits>
 
 namespace efunc {
 
@@ -1391,7 +1392,6 @@ template <int DEG>
 __device__ __forceinline__ void fwd_quad(const TileSmem<DEG>& S, int n, int ph, int Sf, int j, const float4 q,
                                          const float M, float& e, float& m)
 {
-#pragma unroll 2
     for (int k0 = ph; k0 < n; k0 += 4 * Sf) {
         const int k = k0 + j * Sf, kr = min(k, n - 1);
         const float4 kc = S.kc[kr], kv = S.kv[kr];
@@ -2930,21 +2930,26 @@ __global__ __launch_bounds__(IP_BLOCK) void k_init_params(float* __restrict__ th
     double w = 0.0, wx = 0.0, wy = 0.0, wz = 0.0;
     if (shift) {
         const int n0 = VL == 64 ? wv : wv * PW + lane / VL;
-        // sample(x, y, z) for this lane's share of the samples
-        auto each = [&](auto sample) {
+        // sample(x, y, z) for this lane's share of the samples; ahead: unrolled (not
+        // possible with a vote of the wave in sample)
+        auto each = [&](auto ahead, auto sample) {
             for (int64_t c0 = 0; c0 < Ns; c0 += IP_CHUNK) {
                 const int cn = (int)min((int64_t)IP_CHUNK, Ns - c0);
                 __syncthreads();
                 for (int i = tid; i < 3 * cn; i += IP_BLOCK) ss[i] = surf[3 * c0 + i];
                 __syncthreads();
+                if constexpr (decltype(ahead)::value) {
 #pragma unroll 4
-                for (int n = n0; n < cn; n += S) sample(ss[3 * n], ss[3 * n + 1], ss[3 * n + 2]);
+                    for (int n = n0; n < cn; n += S) sample(ss[3 * n], ss[3 * n + 1], ss[3 * n + 2]);
+                } else {
+                    for (int n = n0; n < cn; n += S) sample(ss[3 * n], ss[3 * n + 1], ss[3 * n + 2]);
+                }
             }
         };
         // the reference: the smallest float32 squared distance (a common factor
         // of all weights, so its rounding cancels)
         float mf = INFINITY;
-        each([&](float sx, float sy, float sz) {
+        each(std::true_type{}, [&](float sx, float sy, float sz) {
             const float x = fx - sx, y = fy - sy, z = fz - sz;
             mf = fminf(mf, fmaf(x, x, fmaf(y, y, z * z)));
         });
@@ -2960,7 +2965,7 @@ __global__ __launch_bounds__(IP_BLOCK) void k_init_params(float* __restrict__ th
         // of the nearest sample's weight: its distance in double
         if (__syncthreads_or(!(bw * ref * 1e-6 < 100.0))) {
             double md = INFINITY;
-            each([&](float sx, float sy, float sz) {
+            each(std::true_type{}, [&](float sx, float sy, float sz) {
                 const double x = kx - sx, y = ky - sy, z = kz - sz;
                 md = fmin(md, x * x + y * y + z * z);
             });
@@ -2977,7 +2982,7 @@ __global__ __launch_bounds__(IP_BLOCK) void k_init_params(float* __restrict__ th
         // bw (d^2 (1 - e) - r (1 + e)) > cut with e the float32 distances'
         // relative error: certain to weigh below e^-cut
         const float far = (cut / (float)bw + mf * 1.000002f) * 1.000002f;
-        each([&](float sx, float sy, float sz) {
+        each(std::false_type{}, [&](float sx, float sy, float sz) {
             const float x = fx - sx, y = fy - sy, z = fz - sz;
             const float d = fmaf(x, x, fmaf(y, y, z * z));
             if (!__any(!(d > far) || !(d < INFINITY))) return;
