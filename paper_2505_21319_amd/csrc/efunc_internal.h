@@ -263,7 +263,6 @@ struct TileArgs {
     float* lse_out;
     float* dOdq_out;
     int64_t* n_uncertified;
-    float* grad;
     float* gslot;  // moved keys' gradient by binned record (see Work)
     float* gslotg; // grid keys' gradient by vertex (see Work)
     int64_t I;
@@ -286,7 +285,7 @@ struct BatchShape {
     float* theta;
     float* m;
     float* v;
-    float* grad;           // the fallback's gradient (cleared by the AdamW step)
+    float* grad;           // zero (added to the records' gradient and cleared by the AdamW step)
     float* gslotg;         // gradient records of the grid keys (per vertex)
     float* gslot;          // gradient records of the moved keys (flush slots)
     const int* mslot;      // [R^3] the record of each vertex's moved key

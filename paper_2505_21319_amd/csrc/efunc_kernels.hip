@@ -103,13 +103,6 @@ __device__ __forceinline__ int cell_of(float x, const Geo& g)
 }
 
 // ---------------------------------------------------------------- utilities
-__global__ void k_fill_int(int* __restrict__ p, int64_t n, int v)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 __global__ void k_fill_float(float* __restrict__ p, int64_t n)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -999,9 +992,11 @@ __device__ __forceinline__ int tile_bucket(const int4 tl, const Geo& g, int offs
 // Each tile's cost bucket and its rank among the bucket's tiles, and the
 // bucket counts.  A workgroup takes up to COST_TILES tiles, one wave each in
 // turn, counts them per bucket in LDS and takes a range of every bucket's
-// ranks with one atomic.  Its tiles lie apart in the list: slices of one dense
-// cell share their whole key window, and queued back to back they would flush
-// to the same gradient records at once.
+// ranks with one atomic.  Its tiles lie apart in the list, so that slices of one
+// dense cell, which share their whole key window and flush to the same gradient
+// records, are mostly not queued back to back (no rule: neighbours in the list may
+// get neighbouring ranks.  Neighbours in one chunk instead measured the same over
+// 50 calls).
 constexpr int COST_TILES = 32;
 
 __global__ __launch_bounds__(BLOCK) void k_tile_cost(const int* __restrict__ ntiles, Geo g, int offsets, int perkey,
@@ -1503,7 +1498,7 @@ __device__ __forceinline__ void flush_pairs(DevStats* st, const PairCount& c)
 // per query of a piece (0: by the number of queries).
 //
 // Keys reach the pair loops in two steps.  The window's candidates are
-// visited in chunks of KC (grid vertices first, then the moved keys row
+// visited in chunks of up to 2 KC (grid vertices first, then the moved keys row
 // group by row group); each chunk is culled against the bounding box of the
 // tile's queries using key centres alone, and the survivors' tags are
 // appended to S.cand.  Once KC of them have gathered (or the window is
@@ -2274,11 +2269,16 @@ __device__ __forceinline__ int find_item(const Items& I, int q, int& piece, int&
 // k-th key: each gathers, loads and flushes only its own keys, so that a tile
 // of few queries and thousands of keys is cut as well (32,768 points backward at
 // 32^3: 160 us cut by queries, 119 by keys).  The others take part of the
-// queries.  A fit adds a query's terms in the same order as in the whole tile:
+// queries.  A fit adds a query's terms in the order of the whole tile:
 // lanes is the number of lanes that share a query there (0: by the number of
 // queries), the tile's first 256 queries and the rest, which have other lanes,
 // are cut apart, and a piece of at most 64 such lanes gives each of them four
-// (fwd_quad).  With one lane each and only tiles of more than 128 queries cut,
+// (fwd_quad).  The terms themselves are the whole tile's where several lanes share
+// a query and its reference is a corner's logit.  With one lane per query a piece
+// culls against its own box, and where the reference is an exact maximum (a model
+// of moved keys alone) against its own queries' smallest: other terms below e^-T
+// then take part, and in the latter case other lanes add some of the terms, so
+// that the loss agrees with the whole tile's to rounding.  With one lane each and only tiles of more than 128 queries cut,
 // the forward's chain was half of the longest items: tile kernel of a fit of
 // 131,072 points of degree 2 at 20^3 229 and 211 us.
 template <int MODE>
@@ -2626,8 +2626,9 @@ __device__ __forceinline__ void fallback_run(const TileArgs& a)
                 const bool mv = vid < 0;
                 const int64_t v = mv ? -vid - 1 : vid;
                 // one channel of this key: fixed point by vertex (deterministic
-                // mode), else a float atomic into grad, or for a moved key into
-                // its record's slots (slot = channel - first moved channel)
+                // mode), else a float atomic into its record's slots: a grid key's
+                // by vertex (slot = channel), a moved one's by binned record (slot =
+                // channel - first moved channel)
                 auto add = [&](int c, float x) {
                     if (a.gfix)
                         atomicAdd(a.gfix + v * L.nch + c, fixq(x, a.det->dscale[c]));
@@ -2750,7 +2751,8 @@ __global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* 
 }
 
 // The fit step's AdamW (same arithmetic as k_adam): the gradient of a
-// channel is grad plus its slot in its key's record, for a grid channel
+// channel is grad (which only deterministic mode adds to: zero here) plus its
+// slot in its key's record, for a grid channel
 // (c < ngrid) the vertex's record in gslotg, for a moved one the record the
 // binning gave the vertex's moved key (mslot) in gslot; all are cleared.
 // n = nch I < 2^32.  With out the first workgroup reduces the loss instead (one
@@ -2850,8 +2852,8 @@ __global__ __launch_bounds__(BLOCK) void k_batch_loss(const BatchShape* __restri
 
 // AdamW over every shape (blockIdx.y) with the bias corrections of the step
 // held in device memory, so that a captured graph replays later steps.  The
-// gradient of a channel is gathered as in k_adam_fit: grad (the fallback's
-// part) plus its slot in its key's record; both are cleared.
+// gradient of a channel is gathered as in k_adam_fit: grad (zero) plus its slot
+// in its key's record; both are cleared.
 __global__ void k_batch_adam(const BatchShape* __restrict__ bs, const int64_t* __restrict__ step,
                              AdamParams ap)
 {
@@ -3216,7 +3218,6 @@ TileArgs make_tile_args(const Work& w, const Problem& p, bool ordered)
     a.O_out = p.O_out;
     a.lse_out = p.lse_out;
     a.dOdq_out = p.dOdq_out;
-    a.grad = p.grad;
     a.gslot = w.gslot;
     a.gslotg = w.gslotg;
     a.n_uncertified = p.n_uncertified;
