@@ -47,13 +47,13 @@ constexpr int LBIN_PER = 4096;  // queries per LDS-binning workgroup at least
 // its backward by keys and keeps 0: 972,595 points at 38^3 1439 us, with 16 1818.
 // With the gathers counted a fit takes FIT_SHARE: over 78 fits of 60,000 to 400,000
 // points at 24^3 to 80^3 0.75, 0.6, 0.5 and 0.4 gave 3.2, 3.4, 2.0 and -1.1 % over not
-// counting them and cost at worst 18, 3, 7 and 10.  In a batch 0.75 and 0.6 lie within 1 %.
+// counting them and cost at worst 18, 3, 7 and 10.  In a batch 0.75 and 0.6 lie within 2 %.
 // Where no tile is above EVEN shares of the work the launch is balanced as it is and
 // only the cost of the pieces is left, so that the floor is twice as high: without and
 // with, eval of 320,453 near points at 10^3 173 and 143 us (168 uncut), normals of
 // 500,000 there 256 and 210 (236), fit of 274,667 at 9^3 of degree 0 229 and 173 (202).
 // EVEN 2 leaves half of such calls as they were, three times the floor makes others
-// 7 % slower.
+// up to 8 % slower.
 constexpr int MAX_PIECES = 8, MAX_KEY_PIECES = 128;
 constexpr float PIECE_SHARE = 0.75f, FIT_SHARE = 0.6f, DET_SHARE = 1.5f, EVAL_SHARE = 1.3f;
 constexpr float PIECE_LEAST = 1e5f, FIT_LEAST = 1.4e5f, DET_LEAST = 2.5e5f;
